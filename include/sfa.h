@@ -250,7 +250,10 @@ sfa_status sfa_attn_bwd(const void* q_idx, const void* q_val,
 size_t sfa_attn_bwd_workspace(int B, int Hq, int Hkv, int n, int d);
 
 /*
- * Bytes of device workspace sfa_attn_decode needs for these sizes.
+ * Bytes of device workspace sfa_attn_decode needs for these sizes, for any
+ * Hkv and token window.  (A smaller workspace that holds the partials of
+ * 4096-key chunks, B * Hq * ceil(Lmax / 4096) * (d + 2) floats, is taken too;
+ * the context is then never split finer.)
  */
 size_t sfa_attn_decode_workspace(int B, int Hq, int Lmax, int d);
 
@@ -277,10 +280,9 @@ size_t sfa_attn_decode_workspace(int B, int Hq, int Lmax, int d);
  *                 sfa_attn_decode_workspace(B, Hq, Lmax, d) bytes; its
  *                 contents need no initialisation and are scratch after the
  *                 call.  Concurrent calls must use distinct workspaces.
- * d in {64, 128} with Hq / Hkv a power of two runs the tuned kernel (16-byte
- * aligned cache arrays); other d <= 256 and other group sizes run a float32
- * kernel with the same chunks and merge (any Hq / Hkv <= 8, no alignment
- * needs).
+ * d in {64, 128} runs the tuned kernel (any Hq / Hkv <= 8, 16-byte aligned
+ * cache arrays); other d <= 256, and unaligned arrays with Hq / Hkv not a
+ * power of two, run a float32 kernel with a like merge.
  * Limits: B, Hq, Hkv, Lmax >= 1; Lmax <= 2^30; Hq % Hkv == 0; Hq / Hkv <= 8;
  *         B * Hkv <= 65535; 1 <= k <= d <= 256; window, n_global >= 0.
  * Errors: SFA_EINVAL, SFA_ENOTSUP, SFA_ENOSPC (ws_bytes too small), SFA_EHIP.
@@ -310,11 +312,11 @@ sfa_status sfa_attn_decode(const void* q_idx, const void* q_val,
  * shares that GPU's scratch: calls that overlap in time on one GPU (other
  * streams, other threads) race on it and must not be issued.  No part of the
  * scratch needs to start at zero: each partial is written before it is read.
- * Errors: as sfa_attn_decode; SFA_ENOSPC when the partials,
- * sfa_attn_decode_workspace(B, Hq, Lmax, d) bytes, exceed
- * SFA_DECODE_NOALLOC_MAX_BYTES (at d = 128 and 4096-key chunks: B * Hq *
+ * Errors: as sfa_attn_decode; SFA_ENOSPC when the partials of 4096-key
+ * chunks exceed SFA_DECODE_NOALLOC_MAX_BYTES (at d = 128: B * Hq *
  * ceil(Lmax / 4096) <= 64,527 query-head chunks, e.g. 64 sequences x 32
- * heads x 64K keys); SFA_EHIP if the scratch address cannot be looked up.
+ * heads x 64K keys; a finer split that would not fit is not made, by either
+ * entry point); SFA_EHIP if the scratch address cannot be looked up.
  */
 #define SFA_DECODE_NOALLOC_MAX_BYTES ((size_t)32 << 20)
 sfa_status sfa_attn_decode_noalloc(const void* q_idx, const void* q_val,

@@ -6,41 +6,85 @@
 namespace sfa {
 
 // Merge the chunk partials of each (b, h): O = sum_c w_c o_c / sum_c w_c l_c,
-// w_c = 2^(m_c - M), LSE = (M + log2 sum_c w_c l_c) ln 2.
-template <int D>
-__global__ __launch_bounds__(D) void sfa_decode_combine_kernel(
+// w_c = 2^(m_c - M), LSE = (M + log2 sum_c w_c l_c) ln 2.  A few KB of
+// dependent loads per row: each wave takes the maximum and the sum with
+// lanes over the chunks, and the workgroup's T / D groups of D threads (thread
+// = dimension) take every group-count-th chunk of the output sum; the groups'
+// sums are added in order.  T = 512 for more than 16 slots, where one group's
+// sum is a long serial chain (64,000 keys of one sequence: 38.0 -> 35.3 us a
+// step), else one group (2048 rows of 1 to 8 chunks: 4 us less).
+template <int D, int T>
+__global__ __launch_bounds__(T) void sfa_decode_combine_kernel(
     const float* __restrict__ ws_m, const float* __restrict__ ws_l, const float* __restrict__ ws_o,
-    const int32_t* seq_len, int Hq, int Lmax, int nch, int nvc, void* o, int obf16, float* lse) {
+    const int32_t* seq_len, int Hq, int Lmax, int nch, int window, int n_global, int aim, void* o,
+    int obf16, float* lse) {
+  constexpr int NG = T / D;
+  __shared__ float part[NG][D];
   const int bh = blockIdx.x;
   const int b = bh / Hq;
-  const int dd = threadIdx.x;
+  const int dd = threadIdx.x % D, grp = threadIdx.x / D, lane = threadIdx.x & 63;
   const int L = seq_len_of(seq_len, b, Lmax);
-  // slots written this call: the chunks up to L, or the nvc of a window grid
-  const int nc = nvc > 0 ? nvc : (L + kDecChunk - 1) / kDecChunk;
+  const int nc = decode_plan(L, window, n_global, aim).count;
   const int64_t s0 = (int64_t)bh * nch;
   float M = -INFINITY;
-  for (int c = 0; c < nc; ++c) M = fmaxf(M, ws_m[s0 + c]);
+  for (int c = lane; c < nc; c += 64) M = fmaxf(M, ws_m[s0 + c]);
+  M = wave_max_dpp(M);
   const float Mu = (M == -INFINITY) ? 0.f : M;
-  float lsum = 0.f, osum = 0.f;
-  for (int c = 0; c < nc; ++c) {
-    const float w = exp2f(ws_m[s0 + c] - Mu);
-    lsum += w * ws_l[s0 + c];
-    osum += w * ws_o[(s0 + c) * D + dd];
-  }
+  float lsum = 0.f;
+  for (int c = lane; c < nc; c += 64) lsum += exp2f(ws_m[s0 + c] - Mu) * ws_l[s0 + c];
+  lsum = wave_sum(lsum);
+  float osum = 0.f;
+#pragma unroll 4
+  for (int c = grp; c < nc; c += NG) osum += exp2f(ws_m[s0 + c] - Mu) * ws_o[(s0 + c) * D + dd];
+  part[grp][dd] = osum;
+  __syncthreads();
+  if (grp != 0) return;
+#pragma unroll
+  for (int g = 1; g < NG; ++g) osum += part[g][dd];
   const float out = lsum > 0.f ? osum / lsum : 0.f;
   if (obf16) ((uint16_t*)o)[(int64_t)bh * D + dd] = (uint16_t)f32_to_bf16_rne(out);
   else ((float*)o)[(int64_t)bh * D + dd] = out;
   if (lse && dd == 0) lse[bh] = lsum > 0.f ? (M + __log2f(lsum)) * kLn2 : -INFINITY;
 }
 
+static size_t slot_bytes(int B, int Hq, size_t slots, int d) {
+  return (size_t)B * Hq * slots * (size_t)(d + 2) * sizeof(float);
+}
+
+size_t decode_workspace_bytes_min(int B, int Hq, int Lmax, int d) {
+  return slot_bytes(B, Hq, (size_t)((Lmax + kDecodeChunk - 1) / kDecodeChunk), d);
+}
+
+// Whether a step of these sizes may cut sequences below kDecodeChunk keys, and
+// the bytes of the slots it then needs, for any group (a group of kDecMaxG
+// heads and a window have the largest aim), cache format and token window (two slots more than its
+// span of keys: the global keys' last chunk and the window's first are partly
+// filled).  A step whose slots would fit the allocation-free decode's scratch
+// only in chunks of kDecodeChunk keys keeps those, whatever the caller's
+// workspace, so that both entry points give the same bits.
+static bool fine_bytes(int B, int Hq, int Lmax, int d, size_t* bytes) {
+  const int aim = decode_chunks_aim(B, (Hq + kDecMaxG - 1) / kDecMaxG, true, 1);
+  if (aim == 0) return false;
+  const int fine = Lmax / kDecodeMinChunk + (Lmax % kDecodeMinChunk != 0);
+  *bytes = slot_bytes(B, Hq, (size_t)min(fine, decode_slots(Lmax, aim) + 2), d);
+  return *bytes <= noalloc_scratch_bytes() ||
+         decode_workspace_bytes_min(B, Hq, Lmax, d) > noalloc_scratch_bytes();
+}
+
 size_t decode_workspace_bytes(int B, int Hq, int Lmax, int d) {
-  const size_t nch = (size_t)((Lmax + kDecChunk - 1) / kDecChunk);
-  return (size_t)B * Hq * nch * (size_t)(d + 2) * sizeof(float);
+  size_t bytes;
+  return fine_bytes(B, Hq, Lmax, d, &bytes) ? bytes : decode_workspace_bytes_min(B, Hq, Lmax, d);
+}
+
+int decode_aim(int B, int Hq, int Hkv, int Lmax, int d, int window, size_t ws_bytes, bool q8) {
+  size_t bytes;
+  return fine_bytes(B, Hq, Lmax, d, &bytes) && ws_bytes >= bytes
+             ? decode_chunks_aim(B, Hkv, q8, window) : 0;
 }
 
 template <int D, int G, bool VBF16, int KC8, bool C8>
 static void launch_dec_t(const DecParams& p, int B, hipStream_t stream) {
-  dim3 grid(p.nvc > 0 ? p.nvc : p.nch, B * p.Hkv), block(kDecThreads);
+  const dim3 grid(p.nch, B * p.Hkv), block(kDecThreads);
   if (p.table)
     hipLaunchKernelGGL((sfa_decode_kernel<D, G, VBF16, KC8, C8, true>), grid, block, 0, stream, p);
   else
@@ -66,12 +110,10 @@ static void launch_dec_kc(const DecParams& p, int B, hipStream_t stream) {
 
 template <int D, bool VBF16>
 static void launch_dec_g(const DecParams& p, int G, int B, hipStream_t stream) {
-  switch (G) {
-    case 1: launch_dec_kc<D, 1, VBF16>(p, B, stream); break;
-    case 2: launch_dec_kc<D, 2, VBF16>(p, B, stream); break;
-    case 4: launch_dec_kc<D, 4, VBF16>(p, B, stream); break;
-    default: launch_dec_kc<D, 8, VBF16>(p, B, stream); break;
-  }
+  if (G == 1) launch_dec_kc<D, 1, VBF16>(p, B, stream);
+  else if (G == 2) launch_dec_kc<D, 2, VBF16>(p, B, stream);
+  else if (G <= 4) launch_dec_kc<D, 4, VBF16>(p, B, stream);
+  else launch_dec_kc<D, 8, VBF16>(p, B, stream);
 }
 
 int decode_max_group() { return kDecMaxG; }
@@ -81,7 +123,19 @@ DecParams make_dec_params(const DecodeArgs& a) {
   p.q_idx = a.q_idx; p.q_val = a.q_val; p.kc_idx = a.kc_idx; p.kc_val = a.kc_val; p.v = a.v;
   p.seq_len = a.seq_len;
   p.Hq = a.Hq; p.Hkv = a.Hkv; p.Lmax = a.Lmax; p.k = a.k;
-  p.nch = (a.Lmax + kDecChunk - 1) / kDecChunk;
+  p.G = a.Hq / a.Hkv;
+  p.aim = a.aim;
+  p.window = a.window; p.n_global = a.n_global;
+  const int fine = a.Lmax / kDecodeMinChunk + (a.Lmax % kDecodeMinChunk != 0);
+  const int64_t wspan = (int64_t)a.window + a.n_global;
+  const int full = (a.Lmax + kDecodeChunk - 1) / kDecodeChunk;
+  p.nch = decode_slots(a.Lmax, a.aim);
+  if (a.window > 0 && wspan < a.Lmax) {
+    // a sequence still inside the window, or whose query is a global token,
+    // is cut as without one: its length is at most wspan
+    const int w = decode_slots((int)wspan, a.aim) + 2;
+    p.nch = min(w, a.aim == 0 ? full : fine);
+  }
   const size_t nslot = (size_t)a.B * a.Hq * p.nch;
   p.ws_m = (float*)a.ws;
   p.ws_l = p.ws_m + nslot;
@@ -91,29 +145,24 @@ DecParams make_dec_params(const DecodeArgs& a) {
   p.q_dense = a.q_dense;
   p.table = a.table;
   p.max_pages = a.max_pages; p.log2P = a.log2P; p.num_pages = a.num_pages;
-  p.window = a.window; p.n_global = a.n_global;
-  p.nvc = 0;
-  if (a.window > 0) {
-    // the global chunks, the window's chunks (one more when it straddles a
-    // chunk boundary), never more than the whole context
-    const int g = min(a.n_global, a.Lmax);
-    const int v = (g + kDecChunk - 1) / kDecChunk + (a.window + kDecChunk - 1) / kDecChunk + 1;
-    p.nvc = min(v, p.nch);
-  }
   p.kc_scale = a.kc_scale;
   p.v_scale = a.v_scale;
   return p;
 }
 
 hipError_t launch_decode_combine(const DecParams& p, const DecodeArgs& a, hipStream_t stream) {
-  if (a.d == 64)
-    hipLaunchKernelGGL(sfa_decode_combine_kernel<64>, dim3(a.B * a.Hq), dim3(64), 0, stream,
-                       p.ws_m, p.ws_l, p.ws_o, a.seq_len, a.Hq, a.Lmax, p.nch, p.nvc, a.o,
-                       a.obf16, a.lse);
-  else
-    hipLaunchKernelGGL(sfa_decode_combine_kernel<128>, dim3(a.B * a.Hq), dim3(128), 0, stream,
-                       p.ws_m, p.ws_l, p.ws_o, a.seq_len, a.Hq, a.Lmax, p.nch, p.nvc, a.o,
-                       a.obf16, a.lse);
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(a.B * a.Hq), dim3(threads), 0, stream, p.ws_m, p.ws_l, p.ws_o,
+                       a.seq_len, a.Hq, a.Lmax, p.nch, p.window, p.n_global, p.aim, a.o, a.obf16,
+                       a.lse);
+  };
+  if (a.d == 64) {
+    if (p.nch > 16) go(sfa_decode_combine_kernel<64, 512>, 512);
+    else go(sfa_decode_combine_kernel<64, 64>, 64);
+  } else {
+    if (p.nch > 16) go(sfa_decode_combine_kernel<128, 512>, 512);
+    else go(sfa_decode_combine_kernel<128, 128>, 128);
+  }
   return hipGetLastError();
 }
 

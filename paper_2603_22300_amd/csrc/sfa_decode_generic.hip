@@ -231,7 +231,6 @@ __global__ __launch_bounds__(kGdT) void sfa_decode_generic_combine_kernel(
 
 }  // namespace
 
-int decode_generic_max_group() { return kGdMaxG; }
 
 hipError_t launch_attn_decode_generic(const DecodeArgs& a, hipStream_t stream) {
   GDecParams p;

@@ -2,7 +2,19 @@
 //
 // The cache holds sparse key codes (k index/value pairs per key) and dense V.
 // Grid = (context chunks, B * Hkv): a workgroup streams one chunk of one KV
-// head and serves all G query heads of the group from each load.
+// head and serves all G query heads of the group from each load.  A chunk is
+// 4096 keys where the batch fills the chip, and down to 256 (64 per wavefront)
+// where it would not: a sequence is cut as finely as keeps the whole step, all
+// sequences taken as long as this one, within one workgroup per compute unit
+// (a token window or the 8-bit cache: within 8 or 4).  A step of few sequences
+// is bound by the serial chain of one workgroup, not by memory.  Measured per
+// step (32 query over 8 KV heads, d = 128, k = 16), all in 4096-key chunks ->
+// now: one sequence of 3000 keys 40.1 -> 11.0 us (8 -> 96 workgroups), 64,000
+// keys 46.3 -> 33.3; 64 x 16K keys under a 4096-key window 175 -> 153, a
+// 1000-key window 103 -> 51; 8-bit cache with its append, 64 x 4096 keys 125
+// -> 74.  Aiming at 512 or 1024 workgroups without a window was slower (64,000
+// keys 35.0 and 36.7 us, 16 x 2000 keys 21.9 and 23.6 against 20.5): each
+// workgroup pays its prologue and its partial.
 //   scores: lane = key.  The G query codes are densified once into an LDS
 //           table qd[u][h]; a key's score for head h is
 //           scale * sum_t kval_t * qd[kidx_t][h] -- zero-cost for coordinates
@@ -15,7 +27,7 @@
 // Cache layouts: contiguous [B, Hkv, Lmax, ...], or paged -- a pool of pages
 // [num_pages, Hkv, P, ...] with a block table mapping each run of P
 // positions of a sequence to a page (P a power of two >= 16).  A wave's
-// 1024-position range spans at most 64 pages; their ids are loaded once into
+// range of at most 1024 positions spans at most 64 pages; their ids are loaded once into
 // one register (lane l: the range's l-th page) and read back by lane shuffle
 // for the codes (lane = key) and by readlane for V, whose keys within one
 // wide load always share a page.
@@ -31,7 +43,6 @@ namespace sfa {
 
 constexpr int kDecWaves = 4;
 constexpr int kDecThreads = 64 * kDecWaves;
-constexpr int kDecChunk = kDecodeChunk;  // keys per workgroup
 constexpr int kDecMaxG = 8;
 
 struct DecParams {
@@ -44,14 +55,16 @@ struct DecParams {
   float* ws_m;  // [B*Hq, nch]
   float* ws_l;  // [B*Hq, nch]
   float* ws_o;  // [B*Hq, nch, D]
-  int Hq, Hkv, Lmax, k, nch;  // nch: partial slots per (b, h)
+  int Hq, Hkv, Lmax, k;
+  int G;    // query heads per KV head (the kernel's G is the next power of two)
+  int nch;  // partial slots per (b, h), and chunks of the grid
+  int aim;  // chunks per sequence aimed at (decode_chunks_aim)
   float scale_log2;
   int qifmt, qvfmt, kifmt, kvfmt;
   const float* q_dense;   // [B, Hq, D] or null (then q_idx / q_val)
   const int32_t* table;   // paged: [B, max_pages]
   int max_pages, log2P, num_pages;
   int window, n_global;   // token pattern (window 0: all cached keys)
-  int nvc;                // window: workgroups per (b, KV head) (0: nch)
   // 8-bit cache: int8 code values and value rows, one float32 scale per row
   const float* kc_scale;  // [cache rows]
   const float* v_scale;   // [cache rows]
@@ -68,8 +81,43 @@ __device__ __forceinline__ int seq_len_of(const int32_t* seq_len, int b, int Lma
   return L < 0 ? 0 : (L > Lmax ? Lmax : L);
 }
 
+// How a sequence of L keys is cut into chunks.  Without a token window, or for
+// a query that is a global token, chunk x is [x c, (x + 1) c).  With one, the
+// query (position L - 1) sees keys [0, wg) and [wlo, L) only, and the chunks
+// are the ngc that hold the global keys followed by those from number wc0 on.
+// c is the smallest power of two in [256, 4096] for which the keys that are
+// read make at most `aim` chunks.  It depends on the sequence's own length
+// and on B * Hkv only: a paged and a contiguous cache of the same contents
+// are cut alike, whatever their capacities.
+struct DecPlan {
+  int c, count;  // keys per chunk, chunks
+  int wlo, wg, ngc, wc0;
+  bool winq;
+};
+__device__ __forceinline__ DecPlan decode_plan(int L, int window, int n_global, int aim) {
+  DecPlan d;
+  d.winq = window > 0 && L - 1 >= n_global;
+  d.wlo = d.winq ? max(0, L - window) : 0;
+  d.wg = d.winq ? min(n_global, L) : 0;
+  const int span = d.winq ? (int)min((int64_t)L, (int64_t)window + n_global) : L;
+  int lc = 8;  // log2 of 256
+  while (lc < 12 && ((span + (1 << lc) - 1) >> lc) > aim) ++lc;
+  static_assert(kDecodeMinChunk == 1 << 8 && kDecodeChunk == 1 << 12, "chunk range");
+  d.c = 1 << lc;
+  d.count = (L + d.c - 1) >> lc;
+  d.ngc = d.wc0 = 0;
+  if (d.winq) {
+    d.ngc = (d.wg + d.c - 1) >> lc;
+    d.wc0 = max(d.ngc, d.wlo >> lc);
+    d.count = d.ngc + max(0, d.count - d.wc0);
+  }
+  return d;
+}
+
 namespace {
 
+// G: the group's query heads p.G rounded up to a power of two; the heads past
+// p.G have a zero query, and no output.
 // KC8 > 0: cache codes with k = 8 * KC8 in one of two compact formats --
 // int16 indices with bf16 values, or (C8) uint8 indices with float16 values --
 // loaded as 16-byte vectors and prefetched one 64-key sub-block ahead, with
@@ -98,34 +146,35 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: per-wave values stay scalar
+  // Workgroups go round-robin over the 8 XCDs; an even number of chunk slots
+  // rotates with the head, so that the slots past a short sequence's end, or
+  // outside a window's keys, leave no XCD idle (64 x 16K keys under a
+  // 4096-key window in four slots, three in use: 257 us unrotated against
+  // 221 in the same chunks).
   const int bh = blockIdx.y;
+  unsigned slot_u = blockIdx.x;
+  if (gridDim.x % 2 == 0) slot_u = (slot_u + (unsigned)bh + ((unsigned)bh >> 2)) % gridDim.x;
+  const int slot = (int)slot_u;
   const int b = bh / p.Hkv, hkv = bh - b * p.Hkv;
   const int L = seq_len_of(p.seq_len, b, p.Lmax);
-  // Token window: the query (position L - 1) sees keys [0, wg) and [wlo, L)
-  // only.  The grid then covers only the chunks holding them: workgroup x
-  // takes the x-th of the global chunks followed by the window's chunks, and
-  // writes its partial to slot x (past the last such chunk: an empty one).
-  const bool winq = p.window > 0 && L - 1 >= p.n_global;
-  const int wlo = winq ? max(0, L - p.window) : 0;
-  const int wg = winq ? min(p.n_global, L) : 0;
-  int chunk = blockIdx.x;
-  if (winq) {
-    const int ngc = (wg + kDecChunk - 1) / kDecChunk;
-    const int wc0 = max(ngc, wlo / kDecChunk);
-    chunk = chunk < ngc ? chunk : wc0 + (chunk - ngc);
-  }
-  const int c0 = chunk * kDecChunk;  // at most Lmax + 2 chunks: no overflow
-  const int c1 = min(L, c0 + kDecChunk);
+  const DecPlan plan = decode_plan(L, p.window, p.n_global, p.aim);
+  if (slot >= plan.count) return;  // past the sequence: no partial is read from it
+  const bool winq = plan.winq;
+  const int wlo = plan.wlo, wg = plan.wg;
+  int chunk = slot;
+  if (winq && chunk >= plan.ngc) chunk += plan.wc0 - plan.ngc;
+  const int c0 = chunk * plan.c;
+  const int c1 = min(L, c0 + plan.c);
   const int k = p.k;
   const int dmask = D - 1;
 
-  // densify the G query codes: qd[u][h]
+  // densify the query codes: qd[u][h]
   if (p.q_dense) {
     // code each dense query row here: one wavefront per head, kept
     // coordinates keep their float32 value, the rest are zero
     constexpr int E = D / 64;
     for (int h = __builtin_amdgcn_readfirstlane(wave); h < G; h += kDecWaves) {
-      const float* qr = p.q_dense + ((int64_t)b * p.Hq + hkv * G + h) * D;
+      const float* qr = p.q_dense + ((int64_t)b * p.Hq + hkv * p.G + min(h, p.G - 1)) * D;
       uint32_t bits[E], key[E];
       bool sel[E];
 #pragma unroll
@@ -135,14 +184,14 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
       }
       topk_select<E>(key, k, sel);
 #pragma unroll
-      for (int e = 0; e < E; ++e) qd[lane + 64 * e][h] = sel[e] ? __uint_as_float(bits[e]) : 0.f;
+      for (int e = 0; e < E; ++e) qd[lane + 64 * e][h] = sel[e] && h < p.G ? __uint_as_float(bits[e]) : 0.f;
     }
   } else {
     for (int x = tid; x < D * G; x += kDecThreads) (&qd[0][0])[x] = 0.f;
     __syncthreads();
-    for (int x = tid; x < G * k; x += kDecThreads) {
+    for (int x = tid; x < p.G * k; x += kDecThreads) {
       const int h = x / k, t = x - h * k;
-      const int64_t qi = ((int64_t)b * p.Hq + hkv * G + h) * k + t;
+      const int64_t qi = ((int64_t)b * p.Hq + hkv * p.G + h) * k + t;
       const int u = load_idx(p.q_idx, qi, p.qifmt, dmask);
       qd[u][h] = load_val(p.q_val, qi, p.qvfmt);
     }
@@ -161,7 +210,7 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
   const int64_t kv_row0 = ((int64_t)b * p.Hkv + hkv) * p.Lmax;
   const int dsub = lane % DL;  // 8-dim group of this lane in the P.V phase
   const int ksub = lane / DL;  // key offset within a wave-wide V load
-  const int per_wave = kDecChunk / kDecWaves;
+  const int per_wave = plan.c / kDecWaves;
   int w0 = c0 + wave * per_wave;
   int w1 = min(c1, w0 + per_wave);
   // A wave range inside the window's gap does nothing; one that starts in it
@@ -438,7 +487,7 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
   }
   __syncthreads();
   // ---- merge the waves and write this chunk's partial ----
-  for (int x = tid; x < G * D; x += kDecThreads) {
+  for (int x = tid; x < p.G * D; x += kDecThreads) {
     const int h = x / D, dd = x - h * D;
     float M = -INFINITY;
 #pragma unroll
@@ -451,9 +500,9 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
       lsum += sc * red_l[w][h];
       osum += sc * red_o[w][h][dd];
     }
-    const int64_t slot = ((int64_t)b * p.Hq + hkv * G + h) * p.nch + blockIdx.x;
-    p.ws_o[slot * D + dd] = osum;
-    if (dd == 0) { p.ws_m[slot] = M; p.ws_l[slot] = lsum; }
+    const int64_t part = ((int64_t)b * p.Hq + hkv * p.G + h) * p.nch + slot;
+    p.ws_o[part * D + dd] = osum;
+    if (dd == 0) { p.ws_m[part] = M; p.ws_l[part] = lsum; }
   }
 }
 

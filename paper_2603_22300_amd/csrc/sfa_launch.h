@@ -71,20 +71,47 @@ struct DecodeArgs {
   void* o;
   float* lse;
   void* ws;
+  int aim;  // tuned decode: decode_chunks_aim, or 0 where ws holds kDecodeChunk chunks only
   // 8-bit cache (launch_attn_decode_q8): float32 scale per key row / value row
   const float* kc_scale;
   const float* v_scale;
 };
-// Keys per decode workgroup (one context chunk); the workspace holds one
-// partial (m, l, o) per chunk, query head and sequence.
+// Most keys of a decode workgroup (one context chunk), and of the float32
+// decode's; the workspace holds one partial (m, l, o) per chunk, query head
+// and sequence.
 constexpr int kDecodeChunk = 4096;
+// Fewest keys of a chunk (64 per wavefront), and the workgroups that the
+// tuned decode aims at by cutting sequences into smaller chunks (decode_plan):
+// one per compute unit; more for the 8-bit cache, whose waves do more
+// arithmetic per byte, and under a token window, which fills its first and
+// last chunk only partly.
+constexpr int kDecodeMinChunk = 256;
+constexpr int kDecodeTarget = 256, kDecodeTargetQ8 = 1024, kDecodeTargetWindow = 2048;
+// Chunks per (sequence, KV head) that a step over B * Hkv of them aims at.
+// 0 or 1: every chunk has kDecodeChunk keys (B * Hkv alone meets the target).
+inline int decode_chunks_aim(int B, int Hkv, bool q8, int window) {
+  const int target = window > 0 ? kDecodeTargetWindow : q8 ? kDecodeTargetQ8 : kDecodeTarget;
+  return (int)(target / ((int64_t)B * Hkv));
+}
+// Partial slots per (sequence, query head) of a step that reads at most
+// `span` keys of each sequence with that aim (decode_plan).
+inline int decode_slots(int span, int aim) {
+  auto up = [](int a, int b) { return a / b + (a % b != 0); };
+  const int big = up(span, kDecodeChunk), fine = up(span, kDecodeMinChunk);
+  const int most = aim > big ? aim : big;
+  return fine < most ? fine : most;
+}
 hipError_t launch_attn_decode(const DecodeArgs& a, hipStream_t stream);
+// Workspace of any step of these sizes, and of one in chunks of kDecodeChunk
+// keys (never more than the former).
 size_t decode_workspace_bytes(int B, int Hq, int Lmax, int d);
+size_t decode_workspace_bytes_min(int B, int Hq, int Lmax, int d);
+// The aim of a step with a workspace of ws_bytes (at least the minimum).
+int decode_aim(int B, int Hq, int Hkv, int Lmax, int d, int window, size_t ws_bytes, bool q8);
 int decode_max_group();
 // float32 decode for head dimensions without the tuned kernel (d <= 256);
-// same workspace and partial layout, Hq / Hkv <= decode_generic_max_group()
+// same partial layout, in chunks of kDecodeChunk keys; Hq / Hkv <= decode_max_group()
 hipError_t launch_attn_decode_generic(const DecodeArgs& a, hipStream_t stream);
-int decode_generic_max_group();
 
 // Static device scratch of the allocation-free decode (one copy per GPU):
 // its size, and its device address on the current device (looked up once per

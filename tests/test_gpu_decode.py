@@ -81,7 +81,7 @@ def test_other_head_dims(B, Hq, Hkv, Lmax, d, k, v_bf16, seq):
         (2, 10, 2, 700, 64, 8, False, [700, 1]),      # groups of 5 at d = 64
     ])
 def test_group_not_power_of_two(B, Hq, Hkv, Lmax, d, k, v_bf16, seq):
-    """Group sizes that are not a power of two run the float32 decode."""
+    """Group sizes that are not a power of two run the next power of two's kernel."""
     _case(B, Hq, Hkv, Lmax, d, k, v_bf16, seq, seed=Hq + Lmax)
 
 
@@ -117,3 +117,50 @@ def test_decode_64k_full_size_sampled():
         O, Lse = oracle.softmax_attention(qd1, kdd, oracle.widen(np_vals(vc[b, g])), w.scale, False)
         check_o(o[b, h][None], O, TOL_O_BF16V, f"decode O ({b},{h})")
         check_lse(lse[b, h].reshape(1), Lse, f"decode LSE ({b},{h})")
+
+
+@pytest.mark.parametrize(
+    "B,Hq,Hkv,Lmax,d,k,seq,window,n_global",
+    [
+        (1, 8, 2, 1025, 128, 16, [1025], 0, 0),             # 256-key chunks, one key over
+        (3, 4, 1, 1024, 64, 8, [1024, 256, 257], 0, 0),     # at chunk edges
+        (2, 7, 1, 4500, 128, 16, [4500, 0], 0, 0),          # a group of 7, an empty sequence
+        (1, 12, 2, 9000, 64, 16, [8193], 0, 0),             # a group of 6, capacity beyond the length
+        (2, 8, 1, 6000, 128, 16, [6000, 513], 700, 5),      # a window, both sides of its gap
+        (2, 3, 1, 3000, 128, 12, [3000, 301], 256, 300),    # generic codes; a query just past the global tokens
+        (40, 8, 8, 600, 64, 8, None, 0, 0),                 # B * Hkv above the aim: whole chunks
+    ])
+def test_context_split(B, Hq, Hkv, Lmax, d, k, seq, window, n_global):
+    """Sequences cut into chunks below 4096 keys: against the oracle, with the
+    smallest workspace the call takes (4096-key chunks), and bit for bit against
+    the allocation-free entry point."""
+    seed = Lmax + Hq
+    kd = torch.stack([si.normal((Hkv, Lmax, d), seed, "k", b, device=DEV) for b in range(B)])
+    vc = torch.stack([si.normal((Hkv, Lmax, d), seed, "v", b, device=DEV) for b in range(B)]).to(torch.bfloat16)
+    qd = si.normal((B, Hq, d), seed, "q", device=DEV)
+    ci, cv = sfa.sfa_topk_encode(kd, k, idx_dtype=torch.int16, val_dtype=torch.bfloat16)
+    qi, qv = sfa.sfa_topk_encode(qd, k)
+    seq_t = None if seq is None else torch.tensor(seq, dtype=torch.int32, device=DEV)
+    least = B * Hq * -(-Lmax // 4096) * (d + 2) * 4
+    assert least <= sfa.sfa_attn_decode_workspace(B, Hq, Lmax, d)
+    oci, ocv = oracle.topk_encode_bf16(kd.cpu().numpy(), k)
+    oqi, oqv = oracle.topk_encode(qd.cpu().numpy(), k)
+    lens = np.full(B, Lmax) if seq is None else np.array(seq)
+    live = lens > 0
+    O, L = oracle.attn_decode(oqi, oqv, oci, ocv, np_vals(vc), d, 1.0 / math.sqrt(d),
+                              seq_len=np.maximum(lens, 1), window=window, n_global=n_global)
+    O[~live] = 0  # an empty sequence: O = 0, LSE = -inf
+    outs = []
+    for ws in (None, torch.empty(least, dtype=torch.uint8, device=DEV)):
+        o, lse = sfa.sfa_attn_decode(qi, qv, ci, cv, vc, seq_len=seq_t, o_dtype=torch.float32, ws=ws,
+                                     window=window, n_global=n_global)
+        torch.cuda.synchronize()
+        # float32 throughout: 1e-5 as for float32 V, far inside the bf16-V bound
+        check_o(o, O, TOL_O_F32, "split decode O")
+        check_lse(lse[torch.from_numpy(live).to(DEV)], L[live], "split decode LSE")
+        assert torch.isneginf(lse[torch.from_numpy(~live).to(DEV)]).all()
+        outs.append((o, lse))
+    o, lse = torch.empty_like(outs[0][0]), torch.empty_like(outs[0][1])
+    sfa.sfa_attn_decode_noalloc(qi, qv, ci, cv, vc, o, lse=lse, seq_len=seq_t, window=window,
+                                n_global=n_global)
+    assert torch.equal(o, outs[0][0]) and torch.equal(lse, outs[0][1])
