@@ -147,12 +147,15 @@ sfa_status sfa_topk_encode(const float* x, int64_t rows, int d, int k,
  * product instead.  The results agree with the matrix-core path up to float32
  * summation order.
  * Other head dims (d <= 256 except 64 and 128), and group sizes Hq / Hkv
- * that are not a power of two <= 128, run on a float32 vector-unit kernel:
- * overlap sums by code lookups, exact running maximum, float32 probabilities
- * and P.V; any group size, no workspace (ws is then unused).
+ * that are not a power of two <= 128, run on a matrix-core kernel of float32
+ * accuracy without a workspace (ws is then unused), any group size and
+ * alignment: three bfloat16 pieces per code value and every product of order
+ * <= 2 (~2^-24; 16-bit code values with bf16 V exact), V exact (float32 V in
+ * three pieces), the probabilities in three bfloat16 pieces, or in two (~2^-17)
+ * where O is bf16; float32 softmax and accumulation.
  * Limits: B, Hq, Hkv, n >= 1; Hq % Hkv == 0; 1 <= k <= d <= 256;
  *         B * Hkv <= 65535; n * d <= 2^29 and n * k <= 2^29;
- *         on the float32 kernel: B * Hq <= 65535 (SFA_ENOTSUP otherwise);
+ *         on that kernel: B * Hq <= 65535 (SFA_ENOTSUP otherwise);
  *         window, n_global >= 0.
  * Errors: SFA_EINVAL, SFA_ENOTSUP, SFA_ENOSPC (workspace missing or too
  *         small), SFA_EHIP.

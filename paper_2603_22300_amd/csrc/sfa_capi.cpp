@@ -86,8 +86,8 @@ sfa_status sfa_attn_fwd(const void* q_idx, const void* q_val, const void* k_idx,
   if (st != SFA_OK) return st;
   if (window < 0 || n_global < 0) return SFA_EINVAL;
   if ((d != 64 && d != 128) || !pow2_le(Hq / Hkv, sfa::fwd_max_group())) {
-    // head dimensions or group sizes without a matrix-core kernel: the
-    // float32 vector-unit forward (any group size, no workspace)
+    // head dimensions or group sizes without the tuned kernel: the forward of
+    // float32 accuracy (any group size, no workspace)
     if (!sfa::fwd_generic_supported(d, k) || (long long)B * Hq > 65535) return SFA_ENOTSUP;
     return from_hip(sfa::launch_attn_fwd_generic(q_idx, q_val, k_idx, k_val, v, B, Hq, Hkv, n, d,
                                                  k, causal != 0, window,

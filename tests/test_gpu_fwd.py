@@ -124,8 +124,8 @@ def test_index_variant(B, Hq, Hkv, n, d, k, causal, v_bf16):
         (1, 6, 2, 300, 192, 24, True, True),   # d = 192, ten key tiles
     ])
 def test_other_head_dims(B, Hq, Hkv, n, d, k, causal, v_bf16):
-    """Head dimensions other than 64 and 128 run on the float32 vector-unit
-    forward; any group size."""
+    """Head dimensions other than 64 and 128 run on the forward of float32
+    accuracy; any group size."""
     _run_case(B, Hq, Hkv, n, d, k, causal, v_bf16, seed=d * 10 + n)
 
 
@@ -376,3 +376,50 @@ def test_index_variant_repeatable():
     o2, l2 = sfa.sfa_attn_fwd_index(qi, qv, ki, kv, v, o_dtype=torch.float32)
     torch.cuda.synchronize()
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
+
+
+@pytest.mark.parametrize(
+    "B,Hq,Hkv,n,d,k,causal,codes,v_bf16,window,n_global,mag",
+    [
+        (1, 6, 1, 129, 128, 16, True, "f32", True, 0, 0, 1.0),      # one row past a block, groups of 2 of 6
+        (1, 12, 1, 65, 128, 17, True, "f32", True, 0, 0, 1.0),      # groups of 4 of 12, k just past 16
+        (2, 7, 1, 64, 64, 8, False, "i16bf16", True, 0, 0, 1.0),    # 16-bit codes, one whole tile
+        (1, 5, 1, 300, 96, 16, True, "u8f16", True, 70, 5, 1.0),    # fp16 codes, a window and global tokens
+        (1, 2, 2, 333, 96, 12, False, "f32", True, 40, 70, 1.0),    # global tokens past a tile
+        (1, 2, 1, 131, 77, 77, True, "f32", True, 0, 0, 1.0),       # odd d: element loads, k = d
+        (1, 3, 1, 1, 33, 3, True, "f32", False, 0, 0, 1.0),         # n = 1
+        (1, 1, 1, 100, 129, 9, True, "f32", False, 0, 0, 1.0),      # just past the d = 128 kernel, float32 V
+        (1, 3, 3, 200, 256, 256, False, "i16bf16", True, 0, 0, 1.0),  # the largest d and k
+        (1, 6, 2, 200, 128, 16, True, "f32", True, 0, 0, 2.0 ** -30),  # V far below the float16 range
+        (1, 2, 2, 200, 96, 16, True, "f32", True, 0, 0, 2.0 ** 40),    # V far above it
+    ])
+def test_generic_forward_float32_accuracy(B, Hq, Hkv, n, d, k, causal, codes, v_bf16, window,
+                                          n_global, mag):
+    """The forward for other head dims and groups, at the edges of its tiles and
+    formats, to float32 accuracy with a float32 output (1e-5 of the values'
+    scale, the bound of the float32 path) and rounded once with a bf16 one;
+    from arrays 16-byte aligned and not."""
+    it, vt = {"f32": (torch.int32, torch.float32), "i16bf16": (torch.int16, torch.bfloat16),
+              "u8f16": (torch.uint8, torch.float16)}[codes]
+    q, kk, v = si.dense_qkv(B, Hq, Hkv, n, d, 7 * d + n, v_dtype=torch.float32, device=DEV)
+    v = (v * mag).to(torch.bfloat16 if v_bf16 else torch.float32)
+    qi, qv = sfa.sfa_topk_encode(q, k, idx_dtype=it, val_dtype=vt)
+    ki, kv = sfa.sfa_topk_encode(kk, k, idx_dtype=it, val_dtype=vt)
+    scale = 1.0 / math.sqrt(d)
+
+    def wide(x):
+        return x.float().cpu().numpy()
+    O, L = oracle.attn_fwd(qi.cpu().numpy(), wide(qv), ki.cpu().numpy(), wide(kv), np_vals(v), d, scale,
+                           causal, window=window, n_global=n_global)
+    base = torch.zeros(v.numel() + 1, dtype=v.dtype, device=DEV)
+    base[1:] = v.reshape(-1)
+    for vin in (v, base[1:].view(v.shape)):  # the second one element off the allocation
+        o, lse = sfa.sfa_attn_fwd(qi, qv, ki, kv, vin, causal=causal, scale=scale, window=window,
+                                  n_global=n_global, o_dtype=torch.float32)
+        torch.cuda.synchronize()
+        check_o(o / mag, O / mag, TOL_O_F32, "generic O")
+        check_lse(lse, L, "generic LSE", tol=1e-5)
+    o16, _ = sfa.sfa_attn_fwd(qi, qv, ki, kv, v, causal=causal, scale=scale, window=window,
+                              n_global=n_global, o_dtype=torch.bfloat16)
+    # two pieces of P: ~2^-17 of the values' scale beside the output's rounding
+    check_o((o16.float() / mag).to(torch.bfloat16), O / mag, 5e-5, "generic bf16 O")
