@@ -49,6 +49,11 @@ namespace {
 constexpr int kT = 32;         // rows (queries or keys) per tile image
 constexpr int kNW = 8;         // dk, dv: wavefronts per workgroup (two per SIMD)
 constexpr int kNWQ = 8;        // dq: wavefronts per workgroup (two per SIMD)
+// dq at d = 64 with groups of at most 4: three workgroups of four waves on a
+// compute unit, three waves per SIMD, where one of eight waves (155 registers)
+// leaves two.  The register cap is stated: without it the compiler kept the
+// accumulators in AGPRs and moved them to and from VGPRs every tile.
+constexpr int kNWQ64 = 4;
 constexpr float kLog2e = 1.44269504088896340736f;
 
 // Tile images: 32 rows, each row the bf16 pieces of two arrays side by side,
@@ -93,7 +98,7 @@ struct BwdParams {
   int window, n_global;  // token pattern: |i - j| < window or a global token (window 0: none)
   int ifmt, vfmt, vbf16, obf16;
   int nt;    // tiles per head: ceil(n / 32)
-  int BR;    // query positions per dq workgroup: 256 / G
+  int BR;    // query positions per dq workgroup: its rows / G
   int nqb;   // dq workgroups per (batch, KV head)
   int lg;    // log2(G): the matrix-core kernels run power-of-two groups
   int nkb;   // dk / dv key blocks (256 keys) per (batch, KV head)
@@ -176,6 +181,16 @@ __device__ __forceinline__ void xcd_map(int nx, int& x, int& bh) {
     x = j % nx;
     bh = (id & 7) + 8 * (j / nx);
   }
+}
+
+// Short sequences: all blocks of an XCD are resident at once or nearly, and
+// workgroup j of the XCD starts on compute unit j % 32.  Blocks run
+// longest-first per head, so a block count that divides 32 would put blocks of
+// one length on one compute unit; the heads of every other round of 32
+// workgroups take their blocks in the opposite order instead (a permutation of
+// each head's blocks; long sequences, with 32 blocks or more, are left alone).
+__device__ __forceinline__ int snake(int xb, int head, int nblocks) {
+  return (head * nblocks / 32) & 1 && nblocks < 32 ? nblocks - 1 - xb : xb;
 }
 
 // ---------------------------------------------------------------------------
@@ -288,8 +303,10 @@ __device__ __forceinline__ void load_rows_b(const unsigned char* img, int c0, in
 
 // VEX / OEX / CEX: V / dO / the code values are stored in bf16, so their
 // low pieces are zero.
-template <int D, bool VEX, bool OEX, bool CEX>
-__global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
+// NW: wavefronts per workgroup.
+template <int D, bool VEX, bool OEX, bool CEX, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == kNWQ64 ? 3 : 2, NW == kNWQ64 ? 3 : 2)))
+void sfa_bwd_dq_kernel(BwdParams p) {
   using I = Img<D, OEX, VEX>;
   constexpr int NKB = I::NKB, NDB = I::NDB, QRB = I::QRB, KRB = I::KRB, C2 = I::C2;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -311,6 +328,7 @@ __global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
       if (idx >= p.pm) continue;  // last row: the next one breaks
       xb = idx % p.nqb;
       bh = ((int)blockIdx.x & 7) + 8 * (idx / p.nqb);
+      if (p.pm <= p.pr) xb = snake(xb, idx / p.nqb, p.nqb);
       down = prow & 1;
     } else {
       if (prow > 0) break;
@@ -374,7 +392,7 @@ __global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
              (j0 + kT - 1 > pos0 - p.window && j0 < wave_i_max + p.window);
     };
     const unsigned char* kimg0 = p.kimg + (int64_t)bh * p.nt * I::KB;
-    if (nkt > 0) dma<kNWQ>(kimg0 + (int64_t)tile_at(0) * I::KB, smem, I::KB, wave, lane);
+    if (nkt > 0) dma<NW>(kimg0 + (int64_t)tile_at(0) * I::KB, smem, I::KB, wave, lane);
     wait_vm();
     __syncthreads();
     for (int t = 0; t < nkt; ++t) {
@@ -383,25 +401,34 @@ __global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
       // reads through `cur`, the copy of the next tile through `nxt` (restrict:
       // no compiler wait on the copy before the reads)
       auto tile = [&](const unsigned char* __restrict__ cur, unsigned char* __restrict__ nxt) {
-      if (t + 1 < nkt) dma<kNWQ>(kimg0 + (int64_t)tile_at(t + 1) * I::KB, nxt, I::KB, wave, lane);
+      if (t + 1 < nkt) dma<NW>(kimg0 + (int64_t)tile_at(t + 1) * I::KB, nxt, I::KB, wave, lane);
       const int j0 = jt * kT;
       if (wave_ok && (!p.causal || wave_i_max >= j0) && in_window(j0)) {
         const unsigned char* K = cur;
         floatx16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-          bf16x8 a[2], v[2];
+        // each step's operands read one step ahead (the fences keep the
+        // compiler from moving the reads back to their use, a wait at every
+        // one): here, in the last product and in the dK / dV kernels, 32 over 8
+        // heads, n = 16,384: 14.18 -> 13.66 ms, 16-bit codes 10.37 -> 9.92
+        bf16x8 a[2][2], v[2][2];
+        auto kv_load = [&](bf16x8 (&x)[2], bf16x8 (&y)[2], int kb) {
 #pragma unroll
           for (int pc = 0; pc < 2; ++pc) {
-            a[pc] = row_operand(K, ko, kb, pc * D / 8);
-            v[pc] = pc < I::PV ? row_operand(K, ko, kb, C2 + pc * D / 8) : bf16x8{};
+            x[pc] = row_operand(K, ko, kb, pc * D / 8);
+            y[pc] = pc < I::PV ? row_operand(K, ko, kb, C2 + pc * D / 8) : bf16x8{};
           }
+        };
+        kv_load(a[0], v[0], 0);
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+          if (kb + 1 < NKB) kv_load(a[(kb + 1) & 1], v[(kb + 1) & 1], kb + 1);
           const bf16x8 qq[2] = {qB[0][kb], qB[1][kb]};
           const bf16x8 gg[2] = {dB[0][kb], dB[1][kb]};
-          mfma3<!CEX, !CEX>(s, a, qq);   // S^T = K~ Q~^T   (keys x queries)
-          mfma3<!VEX, !OEX>(dp, v, gg);  // dP^T = V dO^T
+          mfma3<!CEX, !CEX>(s, a[kb & 1], qq);   // S^T = K~ Q~^T   (keys x queries)
+          mfma3<!VEX, !OEX>(dp, v[kb & 1], gg);  // dP^T = V dO^T
+          __builtin_amdgcn_sched_barrier(0);
         }
         // dS^T = P^T o (dP^T - D); lane = query my_i, register r = key j0 + 8(r/4) + 4hh + r%4
         // every (row, key) pair of the tile allowed: no element mask (rows past
@@ -423,8 +450,9 @@ __global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
               float pr = __builtin_amdgcn_exp2f(fmaf(s[r + x], p.c, -L2));
               if constexpr (!FULL) {
                 const int j = j0 + 8 * ((r + x) >> 2) + 4 * hh + ((r + x) & 3);
-                const bool ok = row_ok && j < n && (!p.causal || j <= my_i) &&
-                                (!win || abs(my_i - j) < p.window || j < p.n_global || my_i < p.n_global);
+                // (bitwise: no branch per element)
+                const bool ok = row_ok & (j < n) & (!p.causal | (j <= my_i)) &
+                                (!win | (abs(my_i - j) < p.window) | (j < p.n_global) | (my_i < p.n_global));
                 pr = ok ? pr : 0.f;
               }
               ds[x] = pr * (dp[r + x] - Dq);
@@ -442,14 +470,21 @@ __global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
           for (int pc = 0; pc < 2; ++pc) dsb[kk][pc] = __builtin_bit_cast(bf16x8, dsw[kk][pc]);
-        // dQ~^T += K~^T dS^T   (coordinates x queries)
+        // dQ~^T += K~^T dS^T   (coordinates x queries), each step's operands
+        // read one step ahead (the fence keeps the compiler from moving the
+        // reads back to their use)
+        bf16x8 ta[2][2];
+        auto ta_load = [&](bf16x8 (&a)[2], int step) {
+          const int kk = step / NDB, db = step % NDB;
+          a[0] = tr_operand(K, ko, kk, 4 * db);
+          a[1] = tr_operand(K, ko, kk, D / 8 + 4 * db);
+        };
+        ta_load(ta[0], 0);
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-          for (int db = 0; db < NDB; ++db) {
-            const bf16x8 a[2] = {tr_operand(K, ko, kk, 4 * db), tr_operand(K, ko, kk, D / 8 + 4 * db)};
-            mfma3<!CEX, true>(acc[db], a, dsb[kk]);
-          }
+        for (int step = 0; step < 2 * NDB; ++step) {
+          if (step + 1 < 2 * NDB) ta_load(ta[(step + 1) & 1], step + 1);
+          mfma3<!CEX, true>(acc[step % NDB], ta[step & 1], dsb[step / NDB]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       };
@@ -463,7 +498,7 @@ __global__ __launch_bounds__(kNWQ * 64) void sfa_bwd_dq_kernel(BwdParams p) {
     // [wave % 4][query][coordinate], pitch D + 4.
     float* L = (float*)smem + (wave & 3) * kT * (D + 4);
 #pragma unroll
-    for (int round = 0; round < kNWQ / 4; ++round) {
+    for (int round = 0; round < NW / 4; ++round) {
       if (wave / 4 == round) {
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -614,21 +649,25 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
         floatx16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
+        bf16x8 a[2][2], g[2][2];
+        auto qo_load = [&](bf16x8 (&x)[2], bf16x8 (&y)[2], int kb) {
+#pragma unroll
+          for (int pc = 0; pc < 2; ++pc) {
+            x[pc] = row_operand(Q, qo, kb, pc * D / 8);
+            if constexpr (PART == kDK) y[pc] = pc < I::PO ? row_operand(Q, qo, kb, C2 + pc * D / 8) : bf16x8{};
+          }
+        };
+        qo_load(a[0], g[0], 0);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-          bf16x8 a[2];
-#pragma unroll
-          for (int pc = 0; pc < 2; ++pc) a[pc] = row_operand(Q, qo, kb, pc * D / 8);
+          if (kb + 1 < NKB) qo_load(a[(kb + 1) & 1], g[(kb + 1) & 1], kb + 1);
           const bf16x8 kk2[2] = {kB[0][kb], kB[1][kb]};
-          mfma3<!CEX, !CEX>(s, a, kk2);  // S = Q~ K~^T   (queries x keys)
+          mfma3<!CEX, !CEX>(s, a[kb & 1], kk2);  // S = Q~ K~^T   (queries x keys)
           if constexpr (PART == kDK) {
-            bf16x8 g[2];
-#pragma unroll
-            for (int pc = 0; pc < 2; ++pc)
-              g[pc] = pc < I::PO ? row_operand(Q, qo, kb, C2 + pc * D / 8) : bf16x8{};
             const bf16x8 vv2[2] = {vB[0][kb], vB[1][kb]};
-            mfma3<!OEX, !VEX>(dp, g, vv2);  // dP = dO V^T
+            mfma3<!OEX, !VEX>(dp, g[kb & 1], vv2);  // dP = dO V^T
           }
+          __builtin_amdgcn_sched_barrier(0);
         }
         // lane = key my_j; register r = query row q0 + 8(r/4) + 4hh + r%4
         // every (query, key) pair of the tile allowed: no element mask (queries
@@ -658,8 +697,9 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
             float pr = __builtin_amdgcn_exp2f(fmaf(s[r], p.c, -lv[x]));
             if constexpr (!FULL) {
               const int i = q0 + 8 * g4 + 4 * hh + x;
-              const bool ok = key_ok && (!p.causal || i >= my_j) &&
-                              (!win || abs(i - my_j) < p.window || i < p.n_global || my_j < p.n_global);
+              // (bitwise: no branch per element)
+              const bool ok = key_ok & (!p.causal | (i >= my_j)) &
+                              (!win | (abs(i - my_j) < p.window) | (i < p.n_global) | (my_j < p.n_global));
               pr = ok ? pr : 0.f;
             }
             val[x] = PART == kDV ? pr : pr * (dp[r] - dv4[x]);
@@ -683,17 +723,22 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
           for (int pc = 0; pc < 2; ++pc) xb[kk][pc] = __builtin_bit_cast(bf16x8, xw[kk][pc]);
         // dV^T += dO^T P  or  dK~^T += Q~^T dS   (dimensions / coordinates x keys)
         constexpr int ca = PART == kDV ? C2 : 0;  // dO or Q~
+        // each step's operands read one step ahead (dO^T with bf16 dO: the high
+        // piece only)
+        constexpr bool kLo = PART == kDK || I::PO == 2;
+        bf16x8 ta[2][2];
+        auto ta_load = [&](bf16x8 (&a)[2], int step) {
+          const int kk = step / NDB, db = step % NDB;
+          a[0] = tr_operand(Q, qo, kk, ca + 4 * db);
+          a[1] = kLo ? tr_operand(Q, qo, kk, ca + D / 8 + 4 * db) : bf16x8{};
+        };
+        ta_load(ta[0], 0);
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-          for (int db = 0; db < NDB; ++db) {
-            // (dO^T with bf16 dO: the high piece only)
-            const bool lo = PART == kDK || I::PO == 2;
-            const bf16x8 at[2] = {tr_operand(Q, qo, kk, ca + 4 * db),
-                                  lo ? tr_operand(Q, qo, kk, ca + D / 8 + 4 * db) : bf16x8{}};
-            if constexpr (PART == kDV) mfma3<!OEX, true>(acc[db], at, xb[kk]);
-            else mfma3<!CEX, true>(acc[db], at, xb[kk]);
-          }
+        for (int step = 0; step < 2 * NDB; ++step) {
+          if (step + 1 < 2 * NDB) ta_load(ta[(step + 1) & 1], step + 1);
+          if constexpr (PART == kDV) mfma3<!OEX, true>(acc[step % NDB], ta[step & 1], xb[step / NDB]);
+          else mfma3<!CEX, true>(acc[step % NDB], ta[step & 1], xb[step / NDB]);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       };
@@ -752,10 +797,14 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
 // and dK~ accumulators) takes more registers than two waves per SIMD allow,
 // so a workgroup is four waves over 128 keys, at one or two waves per SIMD.
 // LDS holds two stages of the whole query image.  Used at d = 64 with bf16 V
-// and O (gpt2s shape: 0.46 -> 0.38 ms per backward); at d = 128 the single
-// wave per SIMD leaves the dependency chain of a tile (S -> P -> dV, dK)
-// exposed and the two kernels above are faster (66.8 against 82.5 ms on
-// qwen3_32k).
+// and O; at d = 128 the single wave per SIMD leaves the dependency chain of a
+// tile (S -> P -> dV, dK) exposed and the two kernels above are faster (66.8
+// against 82.5 ms on qwen3_32k).  Bound by VALU and matrix-core issue in turn
+// (per tile and wave 163 vector instructions beside 36 MFMAs, 2 waves per SIMD).
+// The wave count per SIMD is stated to the compiler: left free it kept both
+// accumulators in AGPRs, 144 moves per tile, and branched per element of the
+// mask (377 vector instructions).  8 x 12 heads x 1024 tokens: 143 -> 113 us, and
+// 100 with the blocks mixed by length (snake).
 // ---------------------------------------------------------------------------
 constexpr int kNWF = 4;
 static_assert(kNWF * kT <= kSplitKeys, "a split fused block fits the partial results");
@@ -764,7 +813,8 @@ template <int D, bool VEX, bool OEX>
 constexpr bool fused_dkv() { return D == 64 && VEX && OEX; }
 
 template <int D, bool VEX, bool OEX, bool CEX>
-__global__ __launch_bounds__(kNWF * 64) void sfa_bwd_dkvf_kernel(BwdParams p) {
+__global__ __launch_bounds__(kNWF * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void sfa_bwd_dkvf_kernel(BwdParams p) {
   using I = Img<D, OEX, VEX>;
   constexpr int NKB = I::NKB, NDB = I::NDB, QRB = I::QRB, KRB = I::KRB, C2 = I::C2, QB = I::QB;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -774,6 +824,7 @@ __global__ __launch_bounds__(kNWF * 64) void sfa_bwd_dkvf_kernel(BwdParams p) {
   const LaneOff<QRB> qo(lane);
   int xb, bh;
   xcd_map((int)gridDim.x, xb, bh);
+  if (gridDim.y % 8 == 0) xb = snake(xb, bh / 8, (int)gridDim.x);
   // the first p.nsplit items of a head are the parts of key block 0's sweep
   const int seg = xb < p.nsplit ? xb : 0;
   xb = xb < p.nsplit ? 0 : xb - p.nsplit + 1;
@@ -850,18 +901,24 @@ __global__ __launch_bounds__(kNWF * 64) void sfa_bwd_dkvf_kernel(BwdParams p) {
       floatx16 s, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) { s[r] = 0.f; dp[r] = 0.f; }
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) {
-        bf16x8 a[2], g[2];
+      // each step's operands read one step ahead (as in the kernels above)
+      bf16x8 a[2][2], g[2][2];
+      auto qo_load = [&](bf16x8 (&x)[2], bf16x8 (&y)[2], int kb) {
 #pragma unroll
         for (int pc = 0; pc < 2; ++pc) {
-          a[pc] = row_operand(cur, qo, kb, pc * D / 8);
-          g[pc] = pc < I::PO ? row_operand(cur, qo, kb, C2 + pc * D / 8) : bf16x8{};
+          x[pc] = row_operand(cur, qo, kb, pc * D / 8);
+          y[pc] = pc < I::PO ? row_operand(cur, qo, kb, C2 + pc * D / 8) : bf16x8{};
         }
+      };
+      qo_load(a[0], g[0], 0);
+#pragma unroll
+      for (int kb = 0; kb < NKB; ++kb) {
+        if (kb + 1 < NKB) qo_load(a[(kb + 1) & 1], g[(kb + 1) & 1], kb + 1);
         const bf16x8 kk2[2] = {kB[0][kb], kB[1][kb]};
         const bf16x8 vv2[2] = {vB[0][kb], vB[1][kb]};
-        mfma3<!CEX, !CEX>(s, a, kk2);   // S = Q~ K~^T   (queries x keys)
-        mfma3<!OEX, !VEX>(dp, g, vv2);  // dP = dO V^T
+        mfma3<!CEX, !CEX>(s, a[kb & 1], kk2);   // S = Q~ K~^T   (queries x keys)
+        mfma3<!OEX, !VEX>(dp, g[kb & 1], vv2);  // dP = dO V^T
+        __builtin_amdgcn_sched_barrier(0);
       }
       // lane = key my_j; register r = query row q0 + 8(r/4) + 4hh + r%4.
       // Every (query, key) pair of a full tile is allowed: no element mask
@@ -871,8 +928,10 @@ __global__ __launch_bounds__(kNWF * 64) void sfa_bwd_dkvf_kernel(BwdParams p) {
                          jw0 + kT - 1 - q0 >= p.window);
       const bool full = jw0 + kT <= n && (!p.causal || q0 >= jw0 + kT - 1) && !wcut;
       u32x4 pw[2][2], sw[2][2];  // [kk][piece]: P and dS as bf16 pairs
-      // (one body with the mask test per element: the two-body form of the
-      // kernels above costs this kernel its second wave per SIMD)
+      // one straight-line body per case (FULL: no element mask), chosen once
+      // per tile
+      auto px_tile = [&](auto full_c) {
+      constexpr bool FULL = decltype(full_c)::value;
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const float4 l4 = *(const float4*)(l2 + 8 * g4 + 4 * hh);
@@ -884,13 +943,12 @@ __global__ __launch_bounds__(kNWF * 64) void sfa_bwd_dkvf_kernel(BwdParams p) {
         for (int x = 0; x < 4; ++x) {
           const int r = 4 * g4 + x;
           const int i = q0 + 8 * g4 + 4 * hh + x;
-          float pr;
-          if (full) {
-            pr = __builtin_amdgcn_exp2f(fmaf(s[r], p.c, -lv[x]));
-          } else {
-            const bool ok = key_ok && (!p.causal || i >= my_j) &&
-                            (!win || abs(i - my_j) < p.window || i < p.n_global || my_j < p.n_global);
-            pr = ok ? __builtin_amdgcn_exp2f(fmaf(s[r], p.c, -lv[x])) : 0.f;
+          float pr = __builtin_amdgcn_exp2f(fmaf(s[r], p.c, -lv[x]));
+          if constexpr (!FULL) {
+            // (bitwise: no branch per element)
+            const bool ok = key_ok & (!p.causal | (i >= my_j)) &
+                            (!win | (abs(i - my_j) < p.window) | (i < p.n_global) | (my_j < p.n_global));
+            pr = ok ? pr : 0.f;
           }
           pv[x] = pr;
           sv[x] = pr * (dp[r] - dv4[x]);
@@ -907,19 +965,28 @@ __global__ __launch_bounds__(kNWF * 64) void sfa_bwd_dkvf_kernel(BwdParams p) {
           sw[r >> 3][1][(r & 7) >> 1] = lw;
         }
       }
+      };
+      if (full) px_tile(std::true_type{});
+      else px_tile(std::false_type{});
       // dV^T += dO^T P  and  dK~^T += Q~^T dS   (dimensions / coordinates x keys)
+      bf16x8 ao[2][2], aq[2][2];
+      auto to_load = [&](bf16x8 (&x)[2], bf16x8 (&y)[2], int step) {
+        const int kk = step / NDB, db = step % NDB;
+        x[0] = tr_operand(cur, qo, kk, C2 + 4 * db);
+        x[1] = I::PO == 2 ? tr_operand(cur, qo, kk, C2 + D / 8 + 4 * db) : bf16x8{};
+        y[0] = tr_operand(cur, qo, kk, 4 * db);
+        y[1] = tr_operand(cur, qo, kk, D / 8 + 4 * db);
+      };
+      to_load(ao[0], aq[0], 0);
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
+      for (int step = 0; step < 2 * NDB; ++step) {
+        if (step + 1 < 2 * NDB) to_load(ao[(step + 1) & 1], aq[(step + 1) & 1], step + 1);
+        const int kk = step / NDB, db = step % NDB;
         const bf16x8 pb[2] = {__builtin_bit_cast(bf16x8, pw[kk][0]), __builtin_bit_cast(bf16x8, pw[kk][1])};
         const bf16x8 sb[2] = {__builtin_bit_cast(bf16x8, sw[kk][0]), __builtin_bit_cast(bf16x8, sw[kk][1])};
-#pragma unroll
-        for (int db = 0; db < NDB; ++db) {
-          const bf16x8 ao[2] = {tr_operand(cur, qo, kk, C2 + 4 * db),
-                                I::PO == 2 ? tr_operand(cur, qo, kk, C2 + D / 8 + 4 * db) : bf16x8{}};
-          mfma3<!OEX, true>(accV[db], ao, pb);
-          const bf16x8 aq[2] = {tr_operand(cur, qo, kk, 4 * db), tr_operand(cur, qo, kk, D / 8 + 4 * db)};
-          mfma3<!CEX, true>(accK[db], aq, sb);
-        }
+        mfma3<!OEX, true>(accV[db], ao[step & 1], pb);
+        mfma3<!CEX, true>(accK[db], aq[step & 1], sb);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     };
@@ -1000,55 +1067,78 @@ __global__ __launch_bounds__(256) void sfa_bwd_split_sum_kernel(BwdParams p, int
   }
 }
 
+// The dq kernel and its persistent grid.
+template <int D, bool VEX, bool OEX, bool CEX, int NW>
+hipError_t launch_dq(BwdParams p, int B, bool pers, hipStream_t stream) {
+  using I = Img<D, OEX, VEX>;
+  // two key-image stages, or the gather of dQ~ that follows, four waves at a time
+  constexpr int kLds = std::max(2 * I::KB, 4 * kT * (D + 4) * 4);
+  struct Cfg {
+    hipError_t e;
+    int res;  // resident workgroups per XCD
+  };
+  static const Cfg cfg = [] {  // once per instantiation
+    Cfg c{hipSuccess, 0};
+    const void* fn = (const void*)sfa_bwd_dq_kernel<D, VEX, OEX, CEX, NW>;
+    int dev = 0, cus = 0, nb = 0;
+    if (kLds > 65536) c.e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (c.e == hipSuccess) c.e = hipGetDevice(&dev);
+    if (c.e == hipSuccess) c.e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (c.e == hipSuccess) c.e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, NW * 64, kLds);
+    c.res = nb * cus / 8;
+    return c;
+  }();
+  if (cfg.e != hipSuccess) return cfg.e;
+  p.BR = NW * kT / p.G;
+  p.nqb = (p.n + p.BR - 1) / p.BR;
+  p.pm = B * p.Hkv / 8 * p.nqb;
+  p.pr = pers ? max(1, min(cfg.res, p.pm)) : 0;
+  const dim3 grid = pers ? dim3(8 * p.pr) : dim3(p.nqb, B * p.Hkv);
+  hipLaunchKernelGGL((sfa_bwd_dq_kernel<D, VEX, OEX, CEX, NW>), grid, dim3(NW * 64), kLds, stream, p);
+  return hipGetLastError();
+}
+
 template <int D, bool VEX, bool OEX, bool CEX>
 hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   using I = Img<D, OEX, VEX>;
-  // LDS of the dq kernel (two key-image stages, or the gather of dQ~ that
-  // follows, four waves at a time) and of the fused dk / dv kernel (two
-  // query-image stages, or its gather)
-  constexpr int kDqLds = std::max(2 * I::KB, 4 * kT * (D + 4) * 4);
+  // LDS of the fused dk / dv kernel (two query-image stages, or its gather)
   constexpr int kFLds = std::max(2 * I::QB, kNWF * kT * (D + 4) * 4);
   // once per instantiation (a function-local static: initialised once, also
   // under concurrent first calls): kernel attributes, and the resident
   // workgroups per XCD of the persistent grids (per CU x CUs / 8)
   struct Cfg {
     hipError_t e;
-    int res_dq, res_dv, res_dk;
+    int res_dv, res_dk;
   };
   static const Cfg cfg = [] {
-    Cfg c{hipSuccess, 0, 0, 0};
+    Cfg c{hipSuccess, 0, 0};
     hipError_t& e = c.e;
-    const void* fns[5] = {(const void*)sfa_bwd_qprep_kernel<D, OEX>, (const void*)sfa_bwd_kprep_kernel<D, VEX>,
-                          (const void*)sfa_bwd_dq_kernel<D, VEX, OEX, CEX>,
+    const void* fns[4] = {(const void*)sfa_bwd_qprep_kernel<D, OEX>, (const void*)sfa_bwd_kprep_kernel<D, VEX>,
                           (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDV>,
                           (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDK>};
-    const int bytes[5] = {I::QB, I::KB, kDqLds, kQS * I::QB, kQS * I::QB};
-    for (int f = 0; f < 5 && e == hipSuccess; ++f)
+    const int bytes[4] = {I::QB, I::KB, kQS * I::QB, kQS * I::QB};
+    for (int f = 0; f < 4 && e == hipSuccess; ++f)
       if (bytes[f] > 65536) e = hipFuncSetAttribute(fns[f], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[f]);
     if constexpr (fused_dkv<D, VEX, OEX>()) {
       if (e == hipSuccess && kFLds > 65536)
         e = hipFuncSetAttribute((const void*)sfa_bwd_dkvf_kernel<D, VEX, OEX, CEX>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFLds);
     }
-    int dev = 0, cus = 0, nb_dq = 0, nb_dv = 0, nb_dk = 0;
+    int dev = 0, cus = 0, nb_dv = 0, nb_dk = 0;
     if (e == hipSuccess) e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb_dq, (const void*)sfa_bwd_dq_kernel<D, VEX, OEX, CEX>, kNWQ * 64, kDqLds);
     if (e == hipSuccess)
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &nb_dv, (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDV>, kNW * 64, kQS * I::QB);
     if (e == hipSuccess)
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
           &nb_dk, (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDK>, kNW * 64, kQS * I::QB);
-    c.res_dq = nb_dq * cus / 8;
     c.res_dv = nb_dv * cus / 8;
     c.res_dk = nb_dk * cus / 8;
     return c;
   }();
   if (cfg.e != hipSuccess) return cfg.e;
-  const int res_dq = cfg.res_dq, res_dv = cfg.res_dv, res_dk = cfg.res_dk;
+  const int res_dv = cfg.res_dv, res_dk = cfg.res_dk;
   static_assert(kQS * I::QB >= 4 * kT * (D + 4) * 4, "dk gather (four waves at a time) fits the stages");
   static_assert(kQS * I::QB <= 160 * 1024 - 512, "the query-image stages fit LDS");
   static_assert(I::QB / 1024 / kNW >= 1, "each wave copies part of each image");
@@ -1077,13 +1167,15 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   // (not under a token window: there every block sweeps the same number of
   // tiles, and the one-workgroup-per-block grid measured faster)
   const bool pers = (B * p.Hkv) % 8 == 0 && p.window == 0;
-  {
-    BwdParams pq = p;
-    pq.pm = B * p.Hkv / 8 * p.nqb;
-    pq.pr = pers ? max(1, min(res_dq, pq.pm)) : 0;
-    const dim3 gq = pers ? dim3(8 * pq.pr) : dim3(p.nqb, B * p.Hkv);
-    hipLaunchKernelGGL((sfa_bwd_dq_kernel<D, VEX, OEX, CEX>), gq, dim3(kNWQ * 64), kDqLds, stream, pq);
+  hipError_t eq;
+  if constexpr (D == 64) {
+    // a wave's 32 rows must be one head: groups up to the wave count
+    eq = p.G <= kNWQ64 ? launch_dq<D, VEX, OEX, CEX, kNWQ64>(p, B, pers, stream)
+                       : launch_dq<D, VEX, OEX, CEX, kNWQ>(p, B, pers, stream);
+  } else {
+    eq = launch_dq<D, VEX, OEX, CEX, kNWQ>(p, B, pers, stream);
   }
+  if (eq != hipSuccess) return eq;
   static_assert(kFLds <= 160 * 1024, "fused dk/dv stages");
   if constexpr (fused_dkv<D, VEX, OEX>()) {
     const int nkf = (p.n + kNWF * kT - 1) / (kNWF * kT);
@@ -1133,8 +1225,7 @@ hipError_t launch_attn_bwd(const void* q_idx, const void* q_val, const void* k_i
   p.window = window; p.n_global = n_global;
   p.ifmt = ifmt; p.vfmt = vfmt; p.vbf16 = vbf16; p.obf16 = obf16;
   p.nt = (n + kT - 1) / kT;
-  p.BR = kNWQ * kT / p.G;
-  p.nqb = (n + p.BR - 1) / p.BR;
+  p.BR = p.nqb = 0;  // set by launch_dq
   p.lg = __builtin_ctz((unsigned)p.G);  // G is a power of two here (checked by the caller)
   p.nkb = p.pr = p.pm = 0;  // set by launch_d for the dk / dv kernels
   p.nsplit = 1;
