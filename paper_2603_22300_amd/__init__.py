@@ -109,22 +109,28 @@ def sfa_strerror(status: int) -> str:
 _IDX = {torch.int32: SFA_I32, torch.int16: SFA_I16, torch.uint8: SFA_U8}
 _CVAL = {torch.float32: SFA_F32, torch.bfloat16: SFA_BF16, torch.float16: SFA_F16}
 _VAL = {torch.float32: SFA_F32, torch.bfloat16: SFA_BF16}
+# tensors of one dtype
+_F32, _I32, _I8 = {torch.float32: SFA_F32}, {torch.int32: SFA_I32}, {torch.int8: 0}
 
 
 def _check(t: torch.Tensor, name: str, table) -> int:
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor (got {t.device})")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if t.dtype not in table:
+    code = table.get(t.dtype)
+    if code is None:
         raise TypeError(f"{name}: unsupported dtype {t.dtype}")
-    return table[t.dtype]
+    return code
 
 
 def _stream(t: torch.Tensor) -> int:
-    return torch.cuda.current_stream(t.device).cuda_stream
+    # the raw handle of torch's current stream on the tensor's device (what
+    # torch.cuda.current_stream(device).cuda_stream holds, without building the
+    # Stream object: a step of one sequence is as short as these calls)
+    return torch._C._cuda_getCurrentRawStream(t.device.index)
 
 
 def _call(status: int, where: str):
@@ -135,7 +141,7 @@ def _call(status: int, where: str):
 def sfa_topk_encode(x: torch.Tensor, k: int, idx_dtype=torch.int32, val_dtype=torch.float32,
                     idx: torch.Tensor | None = None, val: torch.Tensor | None = None):
     """Row Top-k codes of x [..., d] float32: (idx [..., k], val [..., k])."""
-    _check(x, "x", {torch.float32: SFA_F32})
+    _check(x, "x", _F32)
     d = x.shape[-1]
     rows = x.numel() // d if d else 0
     if idx is None:
@@ -200,7 +206,7 @@ def _fwd(name, q_idx, q_val, k_idx, k_val, v, causal, scale, o_dtype, o, lse, wa
         lse = torch.empty((B, Hq, n), dtype=torch.float32, device=v.device)
     lp = 0
     if lse is not None:
-        _check(lse, "lse", {torch.float32: SFA_F32})
+        _check(lse, "lse", _F32)
         lp = lse.data_ptr()
     mask = [int(bool(causal))]
     if name == "sfa_attn_fwd":
@@ -248,7 +254,7 @@ def sfa_attn_bwd(q_idx, q_val, k_idx, k_val, v, o, lse, dout, causal: bool = Tru
     qt = _check(q_val, "q_val", _CVAL); _check(k_val, "k_val", _CVAL)
     vt = _check(v, "v", _VAL)
     ot = _check(o, "o", _VAL); _check(dout, "dout", _VAL)
-    _check(lse, "lse", {torch.float32: SFA_F32})
+    _check(lse, "lse", _F32)
     if scale is None:
         scale = 1.0 / math.sqrt(d)
     f32 = dict(dtype=torch.float32, device=v.device)
@@ -257,7 +263,7 @@ def sfa_attn_bwd(q_idx, q_val, k_idx, k_val, v, o, lse, dout, causal: bool = Tru
     dv = torch.empty((B, Hkv, n, d), **f32) if dv is None else dv
     for t, name, shape in ((dq, "dq", (B, Hq, n, k)), (dk, "dk", (B, Hkv, n, k)),
                            (dv, "dv", (B, Hkv, n, d))):
-        _check(t, name, {torch.float32: SFA_F32})
+        _check(t, name, _F32)
         if tuple(t.shape) != shape:
             raise ValueError(f"{name} has the wrong shape")
     if ws is None:
@@ -294,7 +300,7 @@ def sfa_attn_decode(q_idx, q_val, kc_idx, kc_val, v_cache, seq_len=None, scale: 
     vt = _check(v_cache, "v_cache", _VAL)
     sp = 0
     if seq_len is not None:
-        _check(seq_len, "seq_len", {torch.int32: SFA_I32})
+        _check(seq_len, "seq_len", _I32)
         if seq_len.numel() != B:
             raise ValueError("seq_len must hold B entries")
         sp = seq_len.data_ptr()
@@ -307,11 +313,11 @@ def sfa_attn_decode(q_idx, q_val, kc_idx, kc_val, v_cache, seq_len=None, scale: 
         lse = torch.empty((B, Hq), dtype=torch.float32, device=v_cache.device)
     lp = 0
     if lse is not None:
-        _check(lse, "lse", {torch.float32: SFA_F32})
+        _check(lse, "lse", _F32)
         lp = lse.data_ptr()
-    need = sfa_attn_decode_workspace(B, Hq, Lmax, d)
     if ws is None:
-        ws = torch.empty(need, dtype=torch.uint8, device=v_cache.device)
+        ws = torch.empty(sfa_attn_decode_workspace(B, Hq, Lmax, d), dtype=torch.uint8,
+                         device=v_cache.device)
     _call(lib().sfa_attn_decode(q_idx.data_ptr(), q_val.data_ptr(), kc_idx.data_ptr(),
                                 kc_val.data_ptr(), v_cache.data_ptr(), sp, B, Hq, Hkv, Lmax, d, k,
                                 float(scale), int(window), int(n_global), qit, qvt, cit, cvt, vt,
@@ -338,13 +344,13 @@ def sfa_attn_decode_noalloc(q_idx, q_val, kc_idx, kc_val, v_cache, o, lse=None, 
     vt = _check(v_cache, "v_cache", _VAL); ot = _check(o, "o", _VAL)
     sp = 0
     if seq_len is not None:
-        _check(seq_len, "seq_len", {torch.int32: SFA_I32})
+        _check(seq_len, "seq_len", _I32)
         if seq_len.numel() != B:
             raise ValueError("seq_len must hold B entries")
         sp = seq_len.data_ptr()
     lp = 0
     if lse is not None:
-        _check(lse, "lse", {torch.float32: SFA_F32})
+        _check(lse, "lse", _F32)
         if lse.numel() != B * Hq:
             raise ValueError("lse must hold B * Hq entries")
         lp = lse.data_ptr()
@@ -359,7 +365,7 @@ def sfa_attn_decode_noalloc(q_idx, q_val, kc_idx, kc_val, v_cache, o, lse=None, 
 
 
 def _i32_vec(t, name: str, n: int) -> int:
-    _check(t, name, {torch.int32: SFA_I32})
+    _check(t, name, _I32)
     if t.numel() != n:
         raise ValueError(f"{name} must hold {n} entries")
     return t.data_ptr()
@@ -375,7 +381,7 @@ def sfa_kv_append(k_new, v_new, seq_len, kc_idx, kc_val, v_cache, k: int, block_
     kc_* [num_pages, Hkv, page_size, k], v_cache [num_pages, Hkv, page_size, d],
     block_table int32 [B, max_pages].  n_new int32 [B] or None (= T)."""
     B, Hkv, T, d = k_new.shape
-    _check(k_new, "k_new", {torch.float32: SFA_F32})
+    _check(k_new, "k_new", _F32)
     vnt = _check(v_new, "v_new", _VAL)
     if tuple(v_new.shape) != (B, Hkv, T, d):
         raise ValueError("v_new must match k_new")
@@ -388,7 +394,7 @@ def sfa_kv_append(k_new, v_new, seq_len, kc_idx, kc_val, v_cache, k: int, block_
     sp = _i32_vec(seq_len, "seq_len", B)
     tp, maxp = 0, 1
     if block_table is not None:
-        _check(block_table, "block_table", {torch.int32: SFA_I32})
+        _check(block_table, "block_table", _I32)
         if block_table.dim() != 2 or block_table.shape[0] != B:
             raise ValueError("block_table must be [B, max_pages]")
         tp, maxp = block_table.data_ptr(), block_table.shape[1]
@@ -416,7 +422,7 @@ def sfa_attn_decode_paged(kc_idx, kc_val, v_cache, block_table, seq_len=None, q=
         raise ValueError("inconsistent cache shapes")
     cit = _check(kc_idx, "kc_idx", _IDX); cvt = _check(kc_val, "kc_val", _CVAL)
     vt = _check(v_cache, "v_cache", _VAL)
-    _check(block_table, "block_table", {torch.int32: SFA_I32})
+    _check(block_table, "block_table", _I32)
     if block_table.dim() != 2:
         raise ValueError("block_table must be [B, max_pages]")
     B, maxp = block_table.shape
@@ -425,7 +431,7 @@ def sfa_attn_decode_paged(kc_idx, kc_val, v_cache, block_table, seq_len=None, q=
     if q is not None:
         if q_idx is not None or q_val is not None:
             raise ValueError("give either q or (q_idx, q_val)")
-        _check(q, "q", {torch.float32: SFA_F32})
+        _check(q, "q", _F32)
         if q.dim() != 3 or q.shape[0] != B or q.shape[2] != d:
             raise ValueError("q must be [B, Hq, d]")
         Hq = q.shape[1]
@@ -449,7 +455,7 @@ def sfa_attn_decode_paged(kc_idx, kc_val, v_cache, block_table, seq_len=None, q=
         lse = torch.empty((B, Hq), dtype=torch.float32, device=v_cache.device)
     lp = 0
     if lse is not None:
-        _check(lse, "lse", {torch.float32: SFA_F32})
+        _check(lse, "lse", _F32)
         lp = lse.data_ptr()
     if ws is None:
         ws = torch.empty(sfa_attn_decode_workspace(B, Hq, maxp * P, d), dtype=torch.uint8,
@@ -473,12 +479,12 @@ def sfa_kv_append_q8(k_new, v_new, seq_len, kc_idx, kc_val, kc_scale, v_cache, v
     [B, Hkv, Lmax]; or paged [num_pages, Hkv, P, ...] with block_table [B,
     max_pages].  seq_len int32 [B] on the GPU is advanced in place."""
     B, Hkv, T, d = k_new.shape
-    _check(k_new, "k_new", {torch.float32: SFA_F32})
+    _check(k_new, "k_new", _F32)
     vt = _check(v_new, "v_new", _VAL)
     cit = _check(kc_idx, "kc_idx", _IDX)
-    _check(kc_val, "kc_val", {torch.int8: 0}); _check(v_cache, "v_cache", {torch.int8: 0})
-    _check(kc_scale, "kc_scale", {torch.float32: SFA_F32})
-    _check(v_scale, "v_scale", {torch.float32: SFA_F32})
+    _check(kc_val, "kc_val", _I8); _check(v_cache, "v_cache", _I8)
+    _check(kc_scale, "kc_scale", _F32)
+    _check(v_scale, "v_scale", _F32)
     P = kc_idx.shape[2]
     if tuple(kc_val.shape) != tuple(kc_idx.shape) or kc_idx.shape[3] != k \
             or tuple(v_cache.shape) != tuple(kc_idx.shape[:3]) + (d,) \
@@ -489,7 +495,7 @@ def sfa_kv_append_q8(k_new, v_new, seq_len, kc_idx, kc_val, kc_scale, v_cache, v
     np_ = _i32_vec(n_new, "n_new", B) if n_new is not None else 0
     tp, max_pages, num_pages = 0, 0, 0
     if block_table is not None:
-        _check(block_table, "block_table", {torch.int32: SFA_I32})
+        _check(block_table, "block_table", _I32)
         tp, max_pages, num_pages = block_table.data_ptr(), block_table.shape[1], kc_idx.shape[0]
     elif kc_idx.shape[0] != B:
         raise ValueError("contiguous cache: first dimension must be B")
@@ -510,19 +516,19 @@ def sfa_attn_decode_q8(kc_idx, kc_val, kc_scale, v_cache, v_scale, block_table=N
     d = v_cache.shape[-1]
     if q is not None:
         B, Hq, _ = q.shape
-        _check(q, "q", {torch.float32: SFA_F32})
+        _check(q, "q", _F32)
         qp, qip, qvp, qit, qvt = q.data_ptr(), 0, 0, 0, 0
     else:
         B, Hq, _ = q_idx.shape
         qit = _check(q_idx, "q_idx", _IDX); qvt = _check(q_val, "q_val", _CVAL)
         qp, qip, qvp = 0, q_idx.data_ptr(), q_val.data_ptr()
     cit = _check(kc_idx, "kc_idx", _IDX)
-    _check(kc_val, "kc_val", {torch.int8: 0}); _check(v_cache, "v_cache", {torch.int8: 0})
-    _check(kc_scale, "kc_scale", {torch.float32: SFA_F32})
-    _check(v_scale, "v_scale", {torch.float32: SFA_F32})
+    _check(kc_val, "kc_val", _I8); _check(v_cache, "v_cache", _I8)
+    _check(kc_scale, "kc_scale", _F32)
+    _check(v_scale, "v_scale", _F32)
     tp, max_pages, num_pages = 0, 0, 0
     if block_table is not None:
-        _check(block_table, "block_table", {torch.int32: SFA_I32})
+        _check(block_table, "block_table", _I32)
         tp, max_pages, num_pages = block_table.data_ptr(), block_table.shape[1], kc_idx.shape[0]
         cap = max_pages * P
     else:
@@ -556,7 +562,7 @@ def sfa_csr_to_codes(indptr, indices, values, d: int, kmax: int, idx_dtype=None,
     rows (idx [rows, kmax] of idx_dtype, default the indices' dtype; val
     [rows, kmax] of the values' dtype), padded with zeros at the lowest free
     coordinates.  Returns (idx, val)."""
-    _check(indptr, "indptr", {torch.int32: SFA_I32})
+    _check(indptr, "indptr", _I32)
     if indptr.dim() != 1 or indptr.numel() < 1:
         raise ValueError("indptr must be 1-D with rows + 1 entries")
     rows = indptr.numel() - 1
