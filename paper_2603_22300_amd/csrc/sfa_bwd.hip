@@ -15,10 +15,9 @@
 // that piece are left out; the sums are unchanged (they only added zeros).
 //
 // Kernels (all on the caller's stream):
-//   sfa_bwd_qprep_kernel  per (batch, query head, 32-row tile): an image of
-//       Q~ and dO as bf16 pieces, plus log2(e) * LSE and D for the 32 rows;
-//   sfa_bwd_kprep_kernel  per (batch, KV head, 32-key tile): an image of K~
-//       and V;
+//   sfa_bwd_prep_kernel   per (batch, query head, 32-row tile): an image of
+//       Q~ and dO as bf16 pieces, plus log2(e) * LSE and D for the 32 rows; per
+//       (batch, KV head, 32-key tile): an image of K~ and V;
 //   sfa_bwd_dq_kernel     query-parallel (like the forward): S^T = K~ Q~^T,
 //       dP^T = V dO^T, dS^T, dQ~^T += K~^T dS^T over the allowed key tiles;
 //   sfa_bwd_dkv_kernel    key-parallel: S = Q~ K~^T, dP = dO V^T, dS,
@@ -111,6 +110,7 @@ struct BwdParams {
   // each, dk_val rows k long) for sfa_bwd_split_sum_kernel to add up.
   int nsplit;
   int bhkv;  // B * Hkv
+  int vec;   // V, O and dO are 16-byte aligned
   float* part_dv;
   float* part_dk;
   float scale, c;  // c = scale * log2(e)
@@ -197,91 +197,114 @@ __device__ __forceinline__ int snake(int xb, int head, int nblocks) {
 // images
 // ---------------------------------------------------------------------------
 
-template <int D, bool OEX>
-__global__ __launch_bounds__(256) void sfa_bwd_qprep_kernel(BwdParams p) {
-  using I = Img<D, OEX>;
-  constexpr int RB = I::QRB;
+// Eight consecutive values from element i on (a multiple of 8), as float32; by
+// 16-byte loads where the array allows (vec).
+__device__ __forceinline__ void load_f8(const void* p, int64_t i, int bf16, int vec, float (&x)[8]) {
+  if (!vec) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = load_f(p, i + e, bf16);
+  } else if (bf16) {
+    const uint4 w = *(const uint4*)((const uint16_t*)p + i);
+    const uint32_t h[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      x[2 * e] = __uint_as_float(h[e] << 16);
+      x[2 * e + 1] = __uint_as_float(h[e] & 0xffff0000u);
+    }
+  } else {
+    const float4 a = *(const float4*)((const float*)p + i), b = *(const float4*)((const float*)p + i + 4);
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+  }
+}
+
+// Eight consecutive values' pieces (LO: the low one too) into row r of an
+// image at columns c8 and c8 + D, 16 bytes each.
+template <int RB, int D, bool LO>
+__device__ __forceinline__ void put_f8(unsigned char* img, int r, int c8, const float (&x)[8]) {
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) split2_pair(x[2 * e], x[2 * e + 1], h[e], l[e]);
+  *(uint4*)(img + img_pos<RB>(r, c8)) = make_uint4(h[0], h[1], h[2], h[3]);
+  if constexpr (LO) *(uint4*)(img + img_pos<RB>(r, D + c8)) = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// One image per workgroup: the query tiles of B * Hq heads (blockIdx.y below
+// that), then the key tiles of B * Hkv heads, in one launch.  Bound by memory
+// latency and the image stores: a tile's rows come as 16-byte loads, all issued
+// before their first use (by elements and
+// in two launches 40 us for 8 x 12 heads x 1024 at d = 64, 730 for 32 over 8
+// heads x 32,768 at d = 128; now 23 and 316).
+template <int D, bool OEX, bool VEX>
+__global__ __launch_bounds__(256) void sfa_bwd_prep_kernel(BwdParams p, int nq) {
+  using I = Img<D, OEX, VEX>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* img = smem;
-  float* l2 = (float*)(smem + I::Q_L2);
-  float* dd = (float*)(smem + I::Q_D);
-  const int t = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;  // bh = b * Hq + hq
+  const int t = blockIdx.x, tid = threadIdx.x;
+  const bool query = (int)blockIdx.y < nq;
+  const int bh = query ? (int)blockIdx.y : (int)blockIdx.y - nq;  // b * Hq + hq, or b * Hkv + hkv
   const int n = p.n, k = p.k;
   const int64_t r0 = (int64_t)bh * n + (int64_t)t * kT;  // first row of the tile
-  for (int i = tid; i < I::QB / 16; i += 256) ((uint4*)smem)[i] = make_uint4(0u, 0u, 0u, 0u);
-  __syncthreads();
-  for (int e = tid; e < kT * k; e += 256) {
-    const int r = e / k;
-    if (t * kT + r >= n) break;
-    const int f = load_idx(p.q_idx, r0 * k + e, p.ifmt, D - 1);
-    uint16_t h, l;
-    split2(load_val(p.q_val, r0 * k + e, p.vfmt), h, l);
-    *(uint16_t*)(img + img_pos<RB>(r, f)) = h;
-    *(uint16_t*)(img + img_pos<RB>(r, D + f)) = l;
-  }
-  // dO pieces, and D = dO . O with 8 threads per row (fixed reduction order)
-  {
-    const int r = tid >> 3, part = tid & 7;
-    const bool ok = t * kT + r < n;
-    float acc = 0.f;
-    for (int x = 0; x < D / 8; ++x) {
-      const int dim = part * (D / 8) + x;
-      float g = 0.f, o = 0.f;
-      if (ok) {
-        g = load_f(p.dout, (r0 + r) * D + dim, p.obf16);
-        o = load_f(p.o, (r0 + r) * D + dim, p.obf16);
+  const int nr = min(kT, n - t * kT);                     // rows of the tile
+  // thread: row tid / 8, dimensions part (D / 8) + 8 c .. + 7 of it
+  const int r = tid >> 3, part = tid & 7;
+  constexpr int NC = D / 64;
+  float x[NC][8], o[NC][8];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[c][e] = o[c][e] = 0.f;
+    const int64_t i = (r0 + r) * D + part * (D / 8) + 8 * c;
+    if (r < nr) {
+      if (query) {
+        load_f8(p.dout, i, p.obf16, p.vec, x[c]);
+        load_f8(p.o, i, p.obf16, p.vec, o[c]);
+      } else {
+        load_f8(p.v, i, p.vbf16, p.vec, x[c]);
       }
-      acc = fmaf(g, o, acc);
-      uint16_t h, l;
-      split2(g, h, l);
-      *(uint16_t*)(img + img_pos<RB>(r, 2 * D + dim)) = h;
-      if constexpr (!OEX) *(uint16_t*)(img + img_pos<RB>(r, 3 * D + dim)) = l;  // (bf16 dO: l = 0)
     }
+  }
+  auto body = [&](auto rb, auto bytes_c, auto lo, const void* ci, const void* cv) {
+    constexpr int RB = decltype(rb)::value, BYTES = decltype(bytes_c)::value;
+    // the codes' part of the rows, and the padding, start at zero
+    for (int i = tid; i < BYTES / 16; i += 256) ((uint4*)smem)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    for (int e = tid; e < nr * k; e += 256) {
+      const int row = e / k;
+      const int f = load_idx(ci, r0 * k + e, p.ifmt, D - 1);
+      uint16_t h, l;
+      split2(load_val(cv, r0 * k + e, p.vfmt), h, l);
+      *(uint16_t*)(img + img_pos<RB>(row, f)) = h;
+      *(uint16_t*)(img + img_pos<RB>(row, D + f)) = l;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) put_f8<RB, D, decltype(lo)::value>(img, r, 2 * D + part * (D / 8) + 8 * c, x[c]);
+  };
+  if (query) {
+    body(std::integral_constant<int, I::QRB>{}, std::integral_constant<int, I::QB>{},
+         std::integral_constant<bool, !OEX>{}, p.q_idx, p.q_val);
+    // D = dO . O with 8 threads per row (fixed reduction order)
+    float acc = 0.f;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc = fmaf(x[c][e], o[c][e], acc);
     acc += __shfl_xor(acc, 1, 64);
     acc += __shfl_xor(acc, 2, 64);
     acc += __shfl_xor(acc, 4, 64);
     if (part == 0) {
       // rows past n: P = exp2(s c - inf) = 0 and D = 0, so they add nothing
-      l2[r] = ok ? p.lse[r0 + r] * kLog2e : INFINITY;
-      dd[r] = ok ? acc : 0.f;
+      ((float*)(smem + I::Q_L2))[r] = r < nr ? p.lse[r0 + r] * kLog2e : INFINITY;
+      ((float*)(smem + I::Q_D))[r] = r < nr ? acc : 0.f;
     }
+  } else {
+    body(std::integral_constant<int, I::KRB>{}, std::integral_constant<int, I::KB>{},
+         std::integral_constant<bool, !VEX>{}, p.k_idx, p.k_val);
   }
   __syncthreads();
-  uint4* dst = (uint4*)(p.qimg + ((int64_t)bh * p.nt + t) * I::QB);
-  for (int i = tid; i < I::QB / 16; i += 256) dst[i] = ((const uint4*)smem)[i];
-}
-
-template <int D, bool VEX>
-__global__ __launch_bounds__(256) void sfa_bwd_kprep_kernel(BwdParams p) {
-  using I = Img<D, false, VEX>;
-  constexpr int RB = I::KRB;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  unsigned char* img = smem;
-  const int t = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;  // bh = b * Hkv + hkv
-  const int n = p.n, k = p.k;
-  const int64_t r0 = (int64_t)bh * n + (int64_t)t * kT;
-  for (int i = tid; i < I::KB / 16; i += 256) ((uint4*)smem)[i] = make_uint4(0u, 0u, 0u, 0u);
-  __syncthreads();
-  for (int e = tid; e < kT * k; e += 256) {
-    const int r = e / k;
-    if (t * kT + r >= n) break;
-    const int f = load_idx(p.k_idx, r0 * k + e, p.ifmt, D - 1);
-    uint16_t h, l;
-    split2(load_val(p.k_val, r0 * k + e, p.vfmt), h, l);
-    *(uint16_t*)(img + img_pos<RB>(r, f)) = h;
-    *(uint16_t*)(img + img_pos<RB>(r, D + f)) = l;
-  }
-  for (int e = tid; e < kT * D; e += 256) {
-    const int r = e / D, dim = e - r * D;
-    if (t * kT + r >= n) break;
-    uint16_t h, l;
-    split2(load_f(p.v, (r0 + r) * D + dim, p.vbf16), h, l);
-    *(uint16_t*)(img + img_pos<RB>(r, 2 * D + dim)) = h;
-    if constexpr (!VEX) *(uint16_t*)(img + img_pos<RB>(r, 3 * D + dim)) = l;  // (bf16 V: l = 0)
-  }
-  __syncthreads();
-  uint4* dst = (uint4*)(p.kimg + ((int64_t)bh * p.nt + t) * I::KB);
-  for (int i = tid; i < I::KB / 16; i += 256) dst[i] = ((const uint4*)smem)[i];
+  const int bytes = query ? I::QB : I::KB;
+  uint4* dst = (uint4*)((query ? p.qimg : p.kimg) + ((int64_t)bh * p.nt + t) * bytes);
+  for (int i = tid; i < bytes / 16; i += 256) dst[i] = ((const uint4*)smem)[i];
 }
 
 // Row operands (lane = row l32, columns 8 c0 + 16 kb + 8 hh ..) of the NP
@@ -1101,6 +1124,7 @@ hipError_t launch_dq(BwdParams p, int B, bool pers, hipStream_t stream) {
 template <int D, bool VEX, bool OEX, bool CEX>
 hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   using I = Img<D, OEX, VEX>;
+  constexpr int kPrepLds = std::max(I::QB, I::KB);
   // LDS of the fused dk / dv kernel (two query-image stages, or its gather)
   constexpr int kFLds = std::max(2 * I::QB, kNWF * kT * (D + 4) * 4);
   // once per instantiation (a function-local static: initialised once, also
@@ -1113,11 +1137,11 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   static const Cfg cfg = [] {
     Cfg c{hipSuccess, 0, 0};
     hipError_t& e = c.e;
-    const void* fns[4] = {(const void*)sfa_bwd_qprep_kernel<D, OEX>, (const void*)sfa_bwd_kprep_kernel<D, VEX>,
+    const void* fns[3] = {(const void*)sfa_bwd_prep_kernel<D, OEX, VEX>,
                           (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDV>,
                           (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDK>};
-    const int bytes[4] = {I::QB, I::KB, kQS * I::QB, kQS * I::QB};
-    for (int f = 0; f < 4 && e == hipSuccess; ++f)
+    const int bytes[3] = {kPrepLds, kQS * I::QB, kQS * I::QB};
+    for (int f = 0; f < 3 && e == hipSuccess; ++f)
       if (bytes[f] > 65536) e = hipFuncSetAttribute(fns[f], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[f]);
     if constexpr (fused_dkv<D, VEX, OEX>()) {
       if (e == hipSuccess && kFLds > 65536)
@@ -1160,9 +1184,14 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
     const int typ = (keys + (p.causal ? 1 : 2) * p.window) / kT + 1;
     p.nsplit = std::min(parts, std::max(1, (p.nt + typ - 1) / typ));
   }
-  const dim3 blk(256);
-  hipLaunchKernelGGL((sfa_bwd_qprep_kernel<D, OEX>), dim3(p.nt, B * p.Hq), blk, I::QB, stream, p);
-  hipLaunchKernelGGL((sfa_bwd_kprep_kernel<D, VEX>), dim3(p.nt, B * p.Hkv), blk, I::KB, stream, p);
+  // (two launches where the heads' sum passes a grid's y limit)
+  const int nq = B * p.Hq, nk = B * p.Hkv;
+  if (nq + nk <= 65535) {
+    hipLaunchKernelGGL((sfa_bwd_prep_kernel<D, OEX, VEX>), dim3(p.nt, nq + nk), dim3(256), kPrepLds, stream, p, nq);
+  } else {
+    hipLaunchKernelGGL((sfa_bwd_prep_kernel<D, OEX, VEX>), dim3(p.nt, nq), dim3(256), kPrepLds, stream, p, nq);
+    hipLaunchKernelGGL((sfa_bwd_prep_kernel<D, OEX, VEX>), dim3(p.nt, nk), dim3(256), kPrepLds, stream, p, 0);
+  }
   // persistent grids when the KV heads split evenly over the 8 XCDs
   // (not under a token window: there every block sweeps the same number of
   // tiles, and the one-workgroup-per-block grid measured faster)
@@ -1230,6 +1259,7 @@ hipError_t launch_attn_bwd(const void* q_idx, const void* q_val, const void* k_i
   p.nkb = p.pr = p.pm = 0;  // set by launch_d for the dk / dv kernels
   p.nsplit = 1;
   p.bhkv = B * Hkv;
+  p.vec = ((uintptr_t)v | (uintptr_t)o | (uintptr_t)dout) % 16 == 0;
   p.part_dv = p.part_dk = nullptr;  // set by launch_d
   p.scale = scale;
   p.c = (float)((double)scale * 1.4426950408889634);

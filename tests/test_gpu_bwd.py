@@ -312,3 +312,29 @@ def test_persistent_grid_sampled(B, Hq, Hkv, n, d, k, causal, bf16, win, ng):
         sel = torch.from_numpy(cols).to(DEV)
         check_grad(dk[b, g, sel], gk, tol, f"dk_val batch {b} KV head {g}")
         check_grad(dv[b, g, sel], gv, tol, f"dv batch {b} KV head {g}")
+
+
+@pytest.mark.parametrize("d,bf16,n,Hq,Hkv,k", [
+    (64, True, 33, 4, 4, 8),      # one row past a tile
+    (64, False, 97, 8, 1, 24),    # float32 V and O, a group of 8, k past 16
+    (128, True, 300, 8, 2, 16),   # several blocks
+    (128, False, 31, 2, 2, 128),  # one ragged tile, k = d
+])
+def test_bwd_unaligned_arrays(d, bf16, n, Hq, Hkv, k):
+    """V, O and dO one element off a 16-byte boundary (element loads in the
+    image pre-pass) give the bits of the aligned arrays."""
+    dt = torch.bfloat16 if bf16 else torch.float32
+    q, kk, v = si.dense_qkv(2, Hq, Hkv, n, d, 5 * n + d, v_dtype=dt, device=DEV)
+    qi, qv = sfa.sfa_topk_encode(q, k)
+    ki, kv = sfa.sfa_topk_encode(kk, k)
+    o, lse = sfa.sfa_attn_fwd(qi, qv, ki, kv, v)
+    do = si.normal(o.shape, 9, "do", device=DEV).to(dt)
+
+    def off(x):
+        base = torch.zeros(x.numel() + 1, dtype=x.dtype, device=DEV)
+        base[1:] = x.reshape(-1)
+        return base[1:].view(x.shape)
+    want = sfa.sfa_attn_bwd(qi, qv, ki, kv, v, o, lse, do)
+    got = sfa.sfa_attn_bwd(qi, qv, ki, kv, off(v), off(o), lse, off(do))
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
