@@ -48,11 +48,14 @@ namespace {
 constexpr int kT = 32;         // rows (queries or keys) per tile image
 constexpr int kNW = 8;         // dk, dv: wavefronts per workgroup (two per SIMD)
 constexpr int kNWQ = 8;        // dq: wavefronts per workgroup (two per SIMD)
-// dq at d = 64 with groups of at most 4: three workgroups of four waves on a
-// compute unit, three waves per SIMD, where one of eight waves (155 registers)
-// leaves two.  The register cap is stated: without it the compiler kept the
-// accumulators in AGPRs and moved them to and from VGPRs every tile.
-constexpr int kNWQ64 = 4;
+// dq with groups of at most 4 (a wave's 32 rows must be one head) also runs
+// workgroups of four waves.  At d = 64 always: three of them on a compute unit,
+// three waves per SIMD, where one of eight waves (155 registers) leaves two.  At
+// d = 128 where eight waves make fewer than 512 workgroups: 2 x 8 heads, n =
+// 1000, whole backward 226 -> 209 us; 32 over 8 heads, n = 2000, 1102 -> 1086.
+// The register cap is stated: without it the compiler kept the accumulators in
+// AGPRs and moved them to and from VGPRs every tile.
+constexpr int kNWQs = 4;
 constexpr float kLog2e = 1.44269504088896340736f;
 
 // Tile images: 32 rows, each row the bf16 pieces of two arrays side by side,
@@ -328,7 +331,7 @@ __device__ __forceinline__ void load_rows_b(const unsigned char* img, int c0, in
 // low pieces are zero.
 // NW: wavefronts per workgroup.
 template <int D, bool VEX, bool OEX, bool CEX, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == kNWQ64 ? 3 : 2, NW == kNWQ64 ? 3 : 2)))
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 4 ? 3 : 2, D == 64 && NW == 4 ? 3 : 2)))
 void sfa_bwd_dq_kernel(BwdParams p) {
   using I = Img<D, OEX, VEX>;
   constexpr int NKB = I::NKB, NDB = I::NDB, QRB = I::QRB, KRB = I::KRB, C2 = I::C2;
@@ -1196,14 +1199,10 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   // (not under a token window: there every block sweeps the same number of
   // tiles, and the one-workgroup-per-block grid measured faster)
   const bool pers = (B * p.Hkv) % 8 == 0 && p.window == 0;
-  hipError_t eq;
-  if constexpr (D == 64) {
-    // a wave's 32 rows must be one head: groups up to the wave count
-    eq = p.G <= kNWQ64 ? launch_dq<D, VEX, OEX, CEX, kNWQ64>(p, B, pers, stream)
-                       : launch_dq<D, VEX, OEX, CEX, kNWQ>(p, B, pers, stream);
-  } else {
-    eq = launch_dq<D, VEX, OEX, CEX, kNWQ>(p, B, pers, stream);
-  }
+  const long long wg8 = (long long)((p.n + kNWQ * kT / p.G - 1) / (kNWQ * kT / p.G)) * B * p.Hkv;
+  const hipError_t eq = p.G <= kNWQs && (D == 64 || wg8 < 512)
+                            ? launch_dq<D, VEX, OEX, CEX, kNWQs>(p, B, pers, stream)
+                            : launch_dq<D, VEX, OEX, CEX, kNWQ>(p, B, pers, stream);
   if (eq != hipSuccess) return eq;
   static_assert(kFLds <= 160 * 1024, "fused dk/dv stages");
   if constexpr (fused_dkv<D, VEX, OEX>()) {
