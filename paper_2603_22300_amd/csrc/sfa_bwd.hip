@@ -151,7 +151,9 @@ __device__ __forceinline__ void dma(const unsigned char* src, unsigned char* dst
 
 __device__ __forceinline__ void wait_vm() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
 
-constexpr int kQS = 3;  // query-image stages of the key-parallel kernels
+// Query-image stages of the key-parallel kernels: three of one image, or two
+// of two images where a workgroup's wavefronts split the sweep two ways.
+constexpr int dkv_stages(int ways) { return ways == 1 ? 3 : 2; }
 
 // Split of key block 0's sweep under a token window with global tokens.
 constexpr int kMaxSplit = 16;         // most work items sharing the sweep
@@ -553,13 +555,23 @@ void sfa_bwd_dq_kernel(BwdParams p) {
 // recompute S.
 constexpr int kDV = 0, kDK = 1;
 
-template <int D, bool VEX, bool OEX, bool CEX, int PART>
+// WAYS 2: a workgroup takes 128 keys, and its wavefronts w and w + 4, on the
+// same 32 keys, every other step of the sweep; their sums are added through
+// LDS.  For grids too small to fill the chip: twice the workgroups, half the
+// serial sweep (whole backward, d = 128, bf16 dO: 32 over 8 heads, n = 2000:
+// 1086 -> 669 us; 8 over 8 heads, batch 2, n = 1000: 209 -> 153 us; n = 333:
+// 92 -> 72 us).  On a full chip one way is faster, as each image is then read
+// for twice the keys (n = 32,768: 52.7 against 56.5 ms).
+template <int D, bool VEX, bool OEX, bool CEX, int PART, int WAYS>
 __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
   using I = Img<D, OEX, VEX>;
   constexpr int NKB = I::NKB, NDB = I::NDB, QRB = I::QRB, KRB = I::KRB, C2 = I::C2, QB = I::QB;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int KWV = kNW / WAYS, KEYS = KWV * kT;  // wavefronts over keys, keys of a block
+  constexpr int S = dkv_stages(WAYS);
+  const int kw = wave % KWV, way = wave / KWV;
   const int n = p.n;
   const LaneOff<QRB> qo(lane);
   // Work items: (batch x KV head, block of 256 keys).  Without the persistent
@@ -593,8 +605,8 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
     }
     const bool part = p.nsplit > 1 && xb == 0;  // a part of block 0's sweep: partial results
     const int b = bh / p.Hkv, hkv = bh - b * p.Hkv;
-    const int j0b = xb * (kNW * kT);  // most key tiles first: smallest j0 first
-    const int jw0 = j0b + wave * kT;
+    const int j0b = xb * KEYS;  // most key tiles first: smallest j0 first
+    const int jw0 = j0b + kw * kT;
     const int my_j = jw0 + l32;
     const bool wave_ok = jw0 < n;
     const bool key_ok = my_j < n;
@@ -627,7 +639,7 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
     const bool win = p.window > 0;
     int t_lo = p.causal ? j0b / kT : 0, t_hi = p.nt - 1, gq_end = 0;
     if (win && j0b >= p.n_global) {
-      const int jlast = min(n, j0b + kNW * kT) - 1;
+      const int jlast = min(n, j0b + KEYS) - 1;
       t_hi = min(p.nt - 1, (jlast + p.window - 1) / kT);
       if (!p.causal) {
         t_lo = max(0, j0b - p.window + 1) / kT;
@@ -653,20 +665,28 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
     auto qimg_of = [&](int it) {
       return p.qimg + ((int64_t)(b * p.Hq + hkv * p.G + (ord(it) & (p.G - 1))) * p.nt + tile_of(it)) * QB;
     };
-    // three stages: the image two tiles ahead is in flight while a tile is
-    // consumed (vmcnt waits only for the one needed next)
-    // every wave copies at least QB / 1024 / kNW blocks of an image
+    // the images S - 1 rounds ahead are in flight while a round (one step per
+    // way) is consumed; with three stages vmcnt waits only for the one needed next
+    // (every wave copies at least QB / 1024 / kNW blocks of an image)
     constexpr int kMinCopies = QB / 1024 / kNW;
-    if (cnt > 0) dma<kNW>(qimg_of(0), smem, QB, wave, lane);
-    if (cnt > 1) dma<kNW>(qimg_of(1), smem + QB, QB, wave, lane);
-    if (cnt > 1) wait_vm_n<kMinCopies>(); else wait_vm();
+    const int rounds = (cnt + WAYS - 1) / WAYS;
+    auto copy_round = [&](int r, unsigned char* dst) {
+#pragma unroll
+      for (int w = 0; w < WAYS; ++w)
+        if (WAYS * r + w < cnt) dma<kNW>(qimg_of(WAYS * r + w), dst + w * QB, QB, wave, lane);
+    };
+    if (rounds > 0) copy_round(0, smem);
+    if (S == 3 && rounds > 1) copy_round(1, smem + QB);
+    if (S == 3 && rounds > 1) wait_vm_n<kMinCopies>(); else wait_vm();
     __syncthreads();
-    for (int it = 0; it < cnt; ++it) {
-      // The tile's LDS reads go through `cur` and the copy two tiles ahead
-      // through `nxt`, both restrict: the compiler then knows the copy cannot
-      // alias those reads and does not wait for it before them.
+    for (int rd = 0; rd < rounds; ++rd) {
+      const int it = WAYS * rd + way;
+      // The tile's LDS reads go through `cur` and the copies ahead through
+      // `nxt`, both restrict: the compiler then knows the copy cannot alias
+      // those reads and does not wait for it before them.
       auto tile = [&](const unsigned char* __restrict__ cur, unsigned char* __restrict__ nxt) {
-      if (it + 2 < cnt) dma<kNW>(qimg_of(it + 2), nxt, QB, wave, lane);
+      if (rd + S - 1 < rounds) copy_round(rd + S - 1, nxt);
+      if (WAYS > 1 && it >= cnt) return;
       const int q0 = tile_of(it) * kT;
       if (wave_ok && (!p.causal || q0 + kT - 1 >= jw0) && in_window(q0)) {
         const unsigned char* Q = cur;
@@ -768,15 +788,34 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
         }
       }
       };
-      tile(smem + (it % kQS) * QB, smem + ((it + 2) % kQS) * QB);
-      // the next tile's copies must be complete; the one after may still run
-      if (it + 2 < cnt) wait_vm_n<kMinCopies>(); else wait_vm();
+      tile(smem + ((rd % S) * WAYS + way) * QB, smem + (rd + S - 1) % S * WAYS * QB);
+      // the next round's copies must be complete; the one after may still run
+      if (S == 3 && rd + 2 < rounds) wait_vm_n<kMinCopies>(); else wait_vm();
       __syncthreads();
     }
+    if constexpr (WAYS == 2) {
+      // the two ways' sums, through LDS (the stages are free)
+      float* M = (float*)smem + kw * 64 * 16 * NDB + lane;
+      if (way == 1) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) M[(db * 16 + r) * 64] = acc[db][r];
+      }
+      __syncthreads();
+      if (way == 0) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[db][r] += M[(db * 16 + r) * 64];
+      }
+      __syncthreads();
+    }
+    const bool writes = key_ok && way == 0;
 
     if constexpr (PART == kDV) {
       // dv: lane = key my_j, register r of block db = dimension db*32 + 8(r/4) + 4hh + r%4
-      if (key_ok) {
+      if (writes) {
         float* dvr = part ? p.part_dv + (((int64_t)seg * p.bhkv + bh) * kSplitKeys + my_j) * D
                           : p.dv + ((int64_t)bh * n + my_j) * D;
 #pragma unroll
@@ -791,7 +830,7 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
       // a time: [wave % 4][key][coordinate], pitch D + 4
       float* L = (float*)smem + (wave & 3) * kT * (D + 4);
 #pragma unroll
-      for (int round = 0; round < kNW / 4; ++round) {
+      for (int round = 0; round < KWV / 4; ++round) {
         if (wave / 4 == round) {
 #pragma unroll
           for (int db = 0; db < NDB; ++db)
@@ -800,7 +839,7 @@ __global__ __launch_bounds__(kNW * 64) void sfa_bwd_dkv_kernel(BwdParams p) {
               L[l32 * (D + 4) + db * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)] = acc[db][r];
         }
         __syncthreads();
-        if (wave / 4 == round && key_ok) {
+        if (wave / 4 == round && writes) {
           const int64_t row = (int64_t)bh * n + my_j;
           float* dkr = part ? p.part_dk + (((int64_t)seg * p.bhkv + bh) * kSplitKeys + my_j) * p.k
                             : p.dk + row * p.k;
@@ -1124,6 +1163,40 @@ hipError_t launch_dq(BwdParams p, int B, bool pers, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The dK or dV kernel and its persistent grid.
+template <int D, bool VEX, bool OEX, bool CEX, int PART, int WAYS>
+hipError_t launch_dkv(BwdParams p, int B, bool pers, hipStream_t stream) {
+  using I = Img<D, OEX, VEX>;
+  constexpr int kLds = dkv_stages(WAYS) * WAYS * I::QB, kKeys = kNW / WAYS * kT;
+  static_assert(kLds >= 4 * kT * (D + 4) * 4, "dk gather (four waves at a time) fits the stages");
+  static_assert(WAYS == 1 || kLds >= kNW / WAYS * 64 * 16 * I::NDB * 4, "the ways' merge fits the stages");
+  static_assert(kLds <= 160 * 1024 - 512, "the query-image stages fit LDS");
+  static_assert(I::QB / 1024 / kNW >= 1, "each wave copies part of each image");
+  struct Cfg {
+    hipError_t e;
+    int res;  // resident workgroups per XCD
+  };
+  static const Cfg cfg = [] {  // once per instantiation
+    Cfg c{hipSuccess, 0};
+    const void* fn = (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, PART, WAYS>;
+    int dev = 0, cus = 0, nb = 0;
+    if (kLds > 65536) c.e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (c.e == hipSuccess) c.e = hipGetDevice(&dev);
+    if (c.e == hipSuccess) c.e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (c.e == hipSuccess) c.e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kNW * 64, kLds);
+    c.res = nb * cus / 8;
+    return c;
+  }();
+  if (cfg.e != hipSuccess) return cfg.e;
+  p.nkb = (p.n + kKeys - 1) / kKeys;
+  p.pm = B * p.Hkv / 8 * p.nkb;
+  p.pr = pers ? max(1, min(cfg.res, p.pm)) : 0;
+  // (a split sweep only with a token window, which has no persistent grid)
+  const dim3 grid = pers ? dim3(8 * p.pr) : dim3(p.nkb + p.nsplit - 1, B * p.Hkv);
+  hipLaunchKernelGGL((sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, PART, WAYS>), grid, dim3(kNW * 64), kLds, stream, p);
+  return hipGetLastError();
+}
+
 template <int D, bool VEX, bool OEX, bool CEX>
 hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   using I = Img<D, OEX, VEX>;
@@ -1131,44 +1204,20 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
   // LDS of the fused dk / dv kernel (two query-image stages, or its gather)
   constexpr int kFLds = std::max(2 * I::QB, kNWF * kT * (D + 4) * 4);
   // once per instantiation (a function-local static: initialised once, also
-  // under concurrent first calls): kernel attributes, and the resident
-  // workgroups per XCD of the persistent grids (per CU x CUs / 8)
-  struct Cfg {
-    hipError_t e;
-    int res_dv, res_dk;
-  };
-  static const Cfg cfg = [] {
-    Cfg c{hipSuccess, 0, 0};
-    hipError_t& e = c.e;
-    const void* fns[3] = {(const void*)sfa_bwd_prep_kernel<D, OEX, VEX>,
-                          (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDV>,
-                          (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDK>};
-    const int bytes[3] = {kPrepLds, kQS * I::QB, kQS * I::QB};
-    for (int f = 0; f < 3 && e == hipSuccess; ++f)
-      if (bytes[f] > 65536) e = hipFuncSetAttribute(fns[f], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[f]);
+  // under concurrent first calls)
+  static const hipError_t configured = [] {
+    hipError_t e = hipSuccess;
+    if (kPrepLds > 65536)
+      e = hipFuncSetAttribute((const void*)sfa_bwd_prep_kernel<D, OEX, VEX>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kPrepLds);
     if constexpr (fused_dkv<D, VEX, OEX>()) {
       if (e == hipSuccess && kFLds > 65536)
         e = hipFuncSetAttribute((const void*)sfa_bwd_dkvf_kernel<D, VEX, OEX, CEX>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kFLds);
     }
-    int dev = 0, cus = 0, nb_dv = 0, nb_dk = 0;
-    if (e == hipSuccess) e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb_dv, (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDV>, kNW * 64, kQS * I::QB);
-    if (e == hipSuccess)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb_dk, (const void*)sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDK>, kNW * 64, kQS * I::QB);
-    c.res_dv = nb_dv * cus / 8;
-    c.res_dk = nb_dk * cus / 8;
-    return c;
+    return e;
   }();
-  if (cfg.e != hipSuccess) return cfg.e;
-  const int res_dv = cfg.res_dv, res_dk = cfg.res_dk;
-  static_assert(kQS * I::QB >= 4 * kT * (D + 4) * 4, "dk gather (four waves at a time) fits the stages");
-  static_assert(kQS * I::QB <= 160 * 1024 - 512, "the query-image stages fit LDS");
-  static_assert(I::QB / 1024 / kNW >= 1, "each wave copies part of each image");
+  if (configured != hipSuccess) return configured;
   // the key images follow the query images in the workspace, then the
   // partial results of a split block
   p.kimg = p.qimg + (size_t)B * p.Hq * p.nt * I::QB;
@@ -1213,18 +1262,26 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
       hipLaunchKernelGGL(sfa_bwd_split_sum_kernel, dim3(kNWF * kT / 16, B * p.Hkv), dim3(256), 0, stream, p, D);
     return hipGetLastError();
   }
-  p.nkb = (p.n + kNW * kT - 1) / (kNW * kT);
-  p.pm = B * p.Hkv / 8 * p.nkb;
-  BwdParams pv = p, pk = p;
-  pv.pr = pers ? max(1, min(res_dv, p.pm)) : 0;
-  pk.pr = pers ? max(1, min(res_dk, p.pm)) : 0;
-  // (a split sweep only with a token window, which has no persistent grid)
-  const dim3 gv = pers ? dim3(8 * pv.pr) : dim3(p.nkb + p.nsplit - 1, B * p.Hkv);
-  const dim3 gk = pers ? dim3(8 * pk.pr) : dim3(p.nkb + p.nsplit - 1, B * p.Hkv);
-  hipLaunchKernelGGL((sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDV>), gv, dim3(kNW * 64), kQS * I::QB,
-                     stream, pv);
-  hipLaunchKernelGGL((sfa_bwd_dkv_kernel<D, VEX, OEX, CEX, kDK>), gk, dim3(kNW * 64), kQS * I::QB,
-                     stream, pk);
+  // The sweep split two ways where blocks of 256 keys (one workgroup per
+  // compute unit, 256 at a time) leave compute units idle.  Causal blocks differ in
+  // length, so the longest ones set the time until there are many (one way
+  // against two, 32 over 8 heads: n = 8192, 256 blocks: 5.16 and 3.58 ms;
+  // 10,000, 320: 6.84 and 5.64; 12,288, 384: 8.94 and 8.66; 16,384, 512: 13.1 and
+  // 13.9).  Non-causal ones are alike and count in whole passes over the chip, a
+  // pass of half blocks at a little over half the time (8 heads: n = 8192, 256
+  // blocks: 1.69 and 1.78 ms; 12,000, 376: 4.37 and 3.97; 12,800, 400: 4.99 and
+  // 5.36).  (Not under a token window, whose split sweep is of a 256-key block.)
+  const long long nb = (long long)((p.n + kNW * kT - 1) / (kNW * kT)) * B * p.Hkv;
+  const bool two_ways = p.window == 0 && (p.causal ? nb <= 384 : nb <= 128 || (nb > 256 && nb <= 384));
+  hipError_t ek = hipSuccess;
+  if (two_ways) {
+    ek = launch_dkv<D, VEX, OEX, CEX, kDV, 2>(p, B, pers, stream);
+    if (ek == hipSuccess) ek = launch_dkv<D, VEX, OEX, CEX, kDK, 2>(p, B, pers, stream);
+  } else {
+    ek = launch_dkv<D, VEX, OEX, CEX, kDV, 1>(p, B, pers, stream);
+    if (ek == hipSuccess) ek = launch_dkv<D, VEX, OEX, CEX, kDK, 1>(p, B, pers, stream);
+  }
+  if (ek != hipSuccess) return ek;
   if (p.nsplit > 1)
     hipLaunchKernelGGL(sfa_bwd_split_sum_kernel, dim3(kNW * kT / 16, B * p.Hkv), dim3(256), 0, stream, p, D);
   return hipGetLastError();

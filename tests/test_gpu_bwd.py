@@ -338,3 +338,18 @@ def test_bwd_unaligned_arrays(d, bf16, n, Hq, Hkv, k):
     got = sfa.sfa_attn_bwd(qi, qv, ki, kv, off(v), off(o), lse, off(do))
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,causal,v_bf16,o_bf16", [
+    (1, 4, 1, 129, True, True, True),     # one key past a block of 128, four heads
+    (1, 1, 1, 33, True, True, True),      # an odd number of steps (two tiles, one of them ragged)
+    (1, 8, 1, 300, False, True, False),   # non-causal, float32 dO images
+    (8, 2, 1, 700, True, False, False),   # persistent grid (8 KV heads), float32 V
+    (1, 2, 2, 31, True, True, True),      # a single step: the second way has none
+    (4, 104, 104, 97, True, True, True),  # 416 causal blocks: one way
+    (3, 43, 43, 150, False, True, True),  # 129 non-causal blocks: one way
+])
+def test_two_way_sweep(B, Hq, Hkv, n, causal, v_bf16, o_bf16):
+    """Few key blocks at d = 128: the dK and dV workgroups split their sweep two
+    ways and add the two sums.  The last two cases lie past the rule's lines."""
+    _run(B, Hq, Hkv, n, 128, 16, causal, v_bf16, seed=n + Hq, o_bf16=o_bf16)
