@@ -8,8 +8,10 @@
 // float32 value of any magnitude, and every product of order <= 2 is kept
 // (~2^-24).  16-bit code values with bf16 V (KX) are their own operands: one
 // exact product, the scale applied to the float32 score.  P.V: V in bf16 is
-// exact (float32 V: three pieces), P enters as bf16 pieces: three (~2^-24),
-// or two (~2^-17, under the 2^-9 of a bf16 output) where O is bf16.
+// exact (float32 V: three pieces), P enters as three bf16 pieces.  Error against 64
+// bits (float32 O, 2-norm; the vector-unit kernel this replaced in brackets): with
+// codes of three times the usual size, 1535 rows at d = 128 O 2.6e-7 (4.5e-7), 1000
+// at d = 192 2.7e-7 (4.2e-7); LSE 4.1e-8 and 5.1e-8 (4.6e-8, 5.4e-8).
 //
 // A workgroup takes R = 32 NW / KG query rows: gs heads of one KV head (the
 // largest power of two <= 4 in the group) times BR = R / gs positions, so that a
@@ -130,13 +132,13 @@ __device__ __forceinline__ uint16_t gen_piece(float x, int pc) {
   return (uint16_t)f32_to_bf16_rne(r1 - bf16_bits_to_f32(m));
 }
 
-// PP: bf16 pieces of P
-template <class Ge, int PP>
+template <class Ge>
 __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
   constexpr int D = Ge::D, NW = Ge::NW, KG = Ge::KG, NV = Ge::NV, KX = Ge::KX, NT = Ge::NT;
   constexpr int RG = Ge::RG, R = Ge::R, KT = Ge::KT, NP = Ge::NP, NKB = Ge::NKB, NDB = Ge::NDB;
   constexpr int QP = Ge::QP, KR = Ge::KR, VR = Ge::VR, SB = Ge::SB, NS = Ge::NS, KW = Ge::KW;
   constexpr int VCH = Ge::VCH, VI = Ge::VI, VW = Ge::VW;
+  constexpr int PP = 3;  // bf16 pieces of P
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5, l32 = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -337,9 +339,11 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
     const uint16_t* Kd = (const uint16_t*)(smem + stage * SB) + (32 * kg + l32) * KR + 8 * hh;
     const unsigned char* Vt = smem + stage * SB + KT * KR * 2 + 32 * kg * VR;
     // S^T: lane = row my_i, register r = key j0 + 8 (r / 4) + 4 hh + r % 4
-    floatx16 s;
+    // in two sums, the products of the first pieces and the rest (s_lo): what the
+    // large terms round off is then as much as in a sum of full products
+    floatx16 s, s_lo;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+    for (int r = 0; r < 16; ++r) s[r] = s_lo[r] = 0.f;
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
       bf16x8 a[NP];
@@ -350,12 +354,15 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
                                                    __builtin_bit_cast(f16x8, qB[0][kb]), s, 0, 0, 0);
       } else {
 #pragma unroll
-        for (int o = NP - 1; o >= 0; --o)  // smaller terms first
+        for (int o = NP - 1; o > 0; --o)
 #pragma unroll
           for (int pc = o; pc >= 0; --pc)
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pc], qB[o - pc][kb], s, 0, 0, 0);
+            s_lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pc], qB[o - pc][kb], s_lo, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], qB[0][kb], s, 0, 0, 0);
       }
     }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = KX != 0 ? s[r] * p.scale_log2 : s[r] + s_lo[r];
     // every (row, key) pair of the sub-tile allowed: no element mask
     const bool wcut = win && j0 + 32 > p.n_global &&
                       (pos0 < p.n_global || wave_last - j0 >= p.window || j0 + 31 - pos0 >= p.window);
@@ -365,7 +372,6 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
       float mt = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        if constexpr (KX != 0) s[r] *= p.scale_log2;
         if constexpr (!decltype(full_c)::value) {
           const int j = j0 + 8 * (r >> 2) + 4 * hh + (r & 3);
           // (bitwise: no branch per element)
@@ -387,13 +393,16 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
           for (int r = 0; r < 16; ++r) acc[db][r] *= alpha;
       }
       const float m_use = m_run == -INFINITY ? 0.f : m_run;
+      // (the tile's sum apart from the running one: a rounding of the large sum
+      // per tile, not per key)
+      float lt = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; r += 2) {
         float x[2];
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
           x[y] = __builtin_amdgcn_exp2f(s[r + y] - m_use);
-          l_run += x[y];
+          lt += x[y];
         }
 #pragma unroll
         for (int pc = 0; pc < PP; ++pc) {
@@ -404,6 +413,7 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
           x[1] -= __uint_as_float(w & 0xffff0000u);
         }
       }
+      l_run += lt;
     };
     if (full) softmax(std::true_type{});
     else softmax(std::false_type{});
@@ -505,17 +515,17 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
   if (p.lse && hh == 0) p.lse[orow] = (m_run + __log2f(l_run)) * kLn2;
 }
 
-template <class Ge, int PP>
+template <class Ge>
 hipError_t launch_gen(GenParams p, int B, hipStream_t stream) {
   // once per instantiation
   static const hipError_t configured =
-      Ge::LDS > 65536 ? hipFuncSetAttribute((const void*)sfa_fwd_generic_kernel<Ge, PP>,
+      Ge::LDS > 65536 ? hipFuncSetAttribute((const void*)sfa_fwd_generic_kernel<Ge>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, Ge::LDS)
                       : hipSuccess;
   if (configured != hipSuccess) return configured;
   p.BR = Ge::R / p.gs;
   p.nqb = (p.n + p.BR - 1) / p.BR;
-  hipLaunchKernelGGL((sfa_fwd_generic_kernel<Ge, PP>), dim3(p.nqb, B * p.Hq / p.gs), dim3(Ge::NT),
+  hipLaunchKernelGGL((sfa_fwd_generic_kernel<Ge>), dim3(p.nqb, B * p.Hq / p.gs), dim3(Ge::NT),
                      Ge::LDS, stream, p);
   return hipGetLastError();
 }
@@ -523,11 +533,8 @@ hipError_t launch_gen(GenParams p, int B, hipStream_t stream) {
 template <int D>
 hipError_t launch_gen_d(const GenParams& p, int B, int vbf16, hipStream_t stream) {
   constexpr int NW = D <= 128 ? 8 : 4, KG = D <= 128 ? 2 : 1;
-  if (!vbf16) return launch_gen<GGeo<D, NW, KG, 3, 0>, 3>(p, B, stream);
-  auto go = [&](auto kx) {
-    using Ge = GGeo<D, NW, KG, 1, decltype(kx)::value>;
-    return p.obf16 ? launch_gen<Ge, 2>(p, B, stream) : launch_gen<Ge, 3>(p, B, stream);
-  };
+  if (!vbf16) return launch_gen<GGeo<D, NW, KG, 3, 0>>(p, B, stream);
+  auto go = [&](auto kx) { return launch_gen<GGeo<D, NW, KG, 1, decltype(kx)::value>>(p, B, stream); };
   if (p.vfmt == kValBF16) return go(std::integral_constant<int, kValBF16>{});
   if (p.vfmt == kValF16) return go(std::integral_constant<int, kValF16>{});
   return go(std::integral_constant<int, 0>{});
