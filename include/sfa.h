@@ -152,7 +152,8 @@ sfa_status sfa_topk_encode(const float* x, int64_t rows, int d, int k,
  * alignment: three bfloat16 pieces per code value and every product of order
  * <= 2 (~2^-24; 16-bit code values with bf16 V exact), V exact (float32 V in
  * three pieces), the probabilities in three bfloat16 pieces; float32 softmax and
- * accumulation.
+ * accumulation.  The pieces hold float32 values from 2^-109 to the largest one in
+ * full, smaller ones to within 2^-134.
  * Limits: B, Hq, Hkv, n >= 1; Hq % Hkv == 0; 1 <= k <= d <= 256;
  *         B * Hkv <= 65535; n * d <= 2^29 and n * k <= 2^29;
  *         on that kernel: B * Hq <= 65535 (SFA_ENOTSUP otherwise);

@@ -4,9 +4,9 @@
 //
 // Scores: the code values (queries with scale * log2(e) folded in, so that a
 // score is a base-2 exponent) are densified as three bfloat16 pieces
-// x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1), which hold a
-// float32 value of any magnitude, and every product of order <= 2 is kept
-// (~2^-24).  16-bit code values with bf16 V (KX) are their own operands: one
+// x0 = bf16(x) (the largest bf16 for a float32 past it), x1 = bf16(x - x0), x2 =
+// bf16(x - x0 - x1), which hold any float32 of magnitude 2^-109 or more, smaller
+// ones to 2^-134, and every product of order <= 2 is kept (~2^-24).  16-bit code values with bf16 V (KX) are their own operands: one
 // exact product, the scale applied to the float32 score.  P.V: V in bf16 is
 // exact (float32 V: three pieces), P enters as three bf16 pieces.  Error against 64
 // bits (float32 O, 2-norm; the vector-unit kernel this replaced in brackets): with
@@ -46,7 +46,7 @@ namespace sfa {
 namespace {
 
 constexpr int kGDmax = 256;
-constexpr float kGLazyMax = 8.f;  // the running maximum is raised past this jump (base-2)
+constexpr float kBf16Max = 0x1.fep127f;
 
 struct GenParams {
   const void* q_idx;
@@ -122,9 +122,9 @@ __device__ __forceinline__ float entry_val(uint32_t raw, int vfmt) {
   return vfmt == kValBF16 ? bf16_bits_to_f32(raw) : f16_bits_to_f32(raw);
 }
 
-// bf16 piece `pc` of x (0: nearest bf16; 1, 2: bf16 of the remaining error)
+// bf16 piece `pc` of x (0: nearest finite bf16; 1, 2: bf16 of the remaining error)
 __device__ __forceinline__ uint16_t gen_piece(float x, int pc) {
-  const uint32_t h = f32_to_bf16_rne(x);
+  const uint32_t h = f32_to_bf16_rne(__builtin_amdgcn_fmed3f(x, -kBf16Max, kBf16Max));
   if (pc == 0) return (uint16_t)h;
   const float r1 = x - bf16_bits_to_f32(h);
   const uint32_t m = f32_to_bf16_rne(r1);
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
         mt = fmaxf(mt, s[r]);
       }
       mt = pair_max(mt);
-      const bool upd = mt > m_run + kGLazyMax;
+      const bool upd = mt > m_run;
       if (__builtin_amdgcn_ballot_w64(upd)) {
         const float alpha = upd ? __builtin_amdgcn_exp2f(m_run - mt) : 1.f;
         m_run = upd ? mt : m_run;

@@ -18,6 +18,7 @@ from helpers import (TOL_LSE, TOL_O_BF16V, TOL_O_F32, check_lse, check_o, np_val
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
+_MAXF = float(np.finfo(np.float32).max)
 _LN2 = math.log(2.0)
 
 
@@ -477,3 +478,50 @@ def test_generic_forward_error_against_64_bits(Hq, Hkv, n, d, k, codes, v_bf16):
         e, b = rel(got, want), rel(plain, want)
         print(f"[parity] general forward {nm}: {e:.2e} against 64 bits, plain float32 {b:.2e}", flush=True)
         assert e <= 1.25 * b, nm
+
+
+@pytest.mark.parametrize("what", ["v", "keys", "queries", "raised maximum"])
+@pytest.mark.parametrize("d", [96, 200])
+def test_generic_forward_extreme_magnitudes(what, d):
+    """Values and products at the ends of the float32 range, where float32 arithmetic
+    stays finite: the largest float32 as V or a code value (past the largest bf16), a
+    running maximum raised by less than 2^8 under V of 2^121."""
+    n, k, scale, causal, vdt, cdt = 96, 4, _LN2, True, torch.float32, torch.float32
+    rng = np.random.default_rng(d)
+    qi = np.tile(np.arange(k), (1, 1, n, 1)); ki = qi.copy()
+    qv = rng.standard_normal((1, 1, n, k)).astype(np.float32); kv = qv[:, :, ::-1].copy()
+    v = rng.standard_normal((1, 1, n, d)).astype(np.float32)
+    if what == "v":  # one such key, in every row's softmax
+        v[0, 0, 0] = np.where(np.arange(d) % 2, _MAXF, -_MAXF)
+    elif what in ("keys", "queries"):  # score of about 4 with its counterpart 2^-126
+        big, small = (kv, qv) if what == "keys" else (qv, kv)
+        small[...] = 0
+        small[..., 0] = 2.0 ** -126
+        big[0, 0, ::3, 0] = _MAXF
+        big[0, 0, 1::3, 0] = -_MAXF
+    elif what == "raised maximum":  # 64 keys of score 0, then one of 7 (base 2)
+        causal = False
+        qv[...] = 0; kv[...] = 0
+        qv[..., 0] = 1.0
+        kv[0, 0, 64, 0] = 7.0
+        v[...] = 1.5 * 2.0 ** 121
+    ti, tv = torch.from_numpy(qi).int().to(DEV), torch.from_numpy(qv).to(cdt).to(DEV)
+    tki, tkv = torch.from_numpy(ki).int().to(DEV), torch.from_numpy(kv).to(cdt).to(DEV)
+    tvv = torch.from_numpy(v).to(vdt).to(DEV)
+    o, lse = sfa.sfa_attn_fwd(ti, tv, tki, tkv, tvv, causal=causal, scale=scale, o_dtype=torch.float32)
+    torch.cuda.synchronize()
+
+    def wide(x):
+        return x.double().cpu().numpy()
+    S = wide(tv)[0, 0] @ wide(tkv)[0, 0].T * np.float32(scale).astype(np.float64)
+    if causal:
+        S[np.triu_indices(n, 1)] = -np.inf
+    m = S.max(1, keepdims=True)
+    P = np.exp(S - m)
+    O = P / P.sum(1, keepdims=True) @ wide(tvv)[0, 0]
+    L = (m + np.log(P.sum(1, keepdims=True)))[:, 0]
+    assert torch.isfinite(o).all() and torch.isfinite(lse).all()
+    mag = np.abs(O).max(1, keepdims=True)
+    assert (np.abs(wide(o)[0, 0] - O) <= TOL_O_F32 * mag).all()
+    # float32 scores: 2^-23 of their size beside the bound of ordinary ones
+    assert (np.abs(wide(lse)[0, 0] - L) <= 1e-5 + 2.0 ** -22 * np.abs(L)).all()
