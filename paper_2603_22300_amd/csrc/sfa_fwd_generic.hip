@@ -7,7 +7,7 @@
 // x0 = bf16(x) (the largest bf16 for a float32 past it), x1 = bf16(x - x0), x2 =
 // bf16(x - x0 - x1), which hold any float32 of magnitude 2^-109 or more, smaller
 // ones to 2^-134, and every product of order <= 2 is kept (~2^-24).  16-bit code values with bf16 V (KX) are their own operands: one
-// exact product, the scale applied to the float32 score.  P.V: V in bf16 is
+// exact product, the scale (bf16: but its power of two) applied to the float32 score.  P.V: V in bf16 is
 // exact (float32 V: three pieces), P enters as three bf16 pieces.  Error against 64
 // bits (float32 O, 2-norm; the vector-unit kernel this replaced in brackets): with
 // codes of three times the usual size, 1535 rows at d = 128 O 2.6e-7 (4.5e-7), 1000
@@ -35,6 +35,8 @@
 // -> 67; 8 heads, n = 1000: d = 256 1545 -> 225, d = 192 with float32 V 1272 ->
 // 300; 5 heads, n = 100: 121 -> 19.  Letting one wavefront of a SIMD stage
 // while the other computes did not change these (150 -> 146, 97 -> 101).
+#include <math.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -57,7 +59,9 @@ struct GenParams {
   void* o;
   float* lse;
   int Hq, Hkv, n, d, k, causal, window, n_global;
-  float scale_log2;  // scale * log2(e)
+  // The factors of the query values and of the scores; their product is scale *
+  // log2(e), so that a score is a base-2 exponent (launch_attn_fwd_generic).
+  float q_mul, s_mul;
   int ifmt, vfmt, obf16;
   int G, gs, BR, nqb;  // group size; heads and positions of a workgroup; blocks per head group
   float inv_k;
@@ -90,7 +94,7 @@ struct GGeo {
 // N code entries as stored, then one of them as (coordinate, value): the loads
 // carry no arithmetic, so that nothing waits for them before they are used.
 // The coordinate is clamped into [0, d): a violated precondition cannot
-// address outside the tables.  RAW: a 16-bit value stays its bit pattern.
+// address outside the tables.
 template <int N>
 __device__ __forceinline__ void load_entries(const void* idx, const void* val, const int64_t (&at)[N],
                                              int ifmt, int vfmt, uint32_t (&ri)[N], uint32_t (&rv)[N]) {
@@ -116,9 +120,8 @@ __device__ __forceinline__ int entry_idx(uint32_t raw, int ifmt, int d) {
   const int u = ifmt == kIdxI16 ? (int)(int16_t)raw : (int)raw;
   return min(max(u, 0), d - 1);
 }
-template <bool RAW>
 __device__ __forceinline__ float entry_val(uint32_t raw, int vfmt) {
-  if (RAW || vfmt == kValF32) return __uint_as_float(raw);
+  if (vfmt == kValF32) return __uint_as_float(raw);
   return vfmt == kValBF16 ? bf16_bits_to_f32(raw) : f16_bits_to_f32(raw);
 }
 
@@ -218,10 +221,10 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
     // (entries past the sequence go to the row's padding, never read)
     auto put = [&](int row, bool ok, uint32_t ri, uint32_t rv) {
       const int f = entry_idx(ri, p.ifmt, d);
-      const float x = entry_val<KX != 0>(rv, p.vfmt);
+      const float x = KX != 0 ? 0.f : entry_val(rv, p.vfmt);
 #pragma unroll
       for (int pc = 0; pc < NP; ++pc)
-        Kd[row * KR + (ok ? pc * D + f : NP * D + pc)] = KX != 0 ? (uint16_t)__float_as_uint(x) : gen_piece(x, pc);
+        Kd[row * KR + (ok ? pc * D + f : NP * D + pc)] = KX != 0 ? (uint16_t)rv : gen_piece(x, pc);
     };
 #pragma unroll
     for (int r = 0; r < 2; ++r)
@@ -297,9 +300,9 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
     load_entries(p.q_idx, p.q_val, at, p.ifmt, p.vfmt, qi, qv);
     auto put = [&](int row, uint32_t ri, uint32_t rv, int pc) {
       if (row < 0) return;
-      const float x = entry_val<KX != 0>(rv, p.vfmt);
+      const float x = p.q_mul * entry_val(rv, p.vfmt);
       Qs[row * QP + entry_idx(ri, p.ifmt, d)] =
-          KX != 0 ? (uint16_t)__float_as_uint(x) : gen_piece(p.scale_log2 * x, pc);
+          KX == kValF16 ? __builtin_bit_cast(uint16_t, (_Float16)x) : gen_piece(x, pc);
     };
 #pragma unroll
     for (int pc = 0; pc < NP; ++pc) {
@@ -362,7 +365,7 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
       }
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = KX != 0 ? s[r] * p.scale_log2 : s[r] + s_lo[r];
+    for (int r = 0; r < 16; ++r) s[r] = KX != 0 ? s[r] * p.s_mul : s[r] + s_lo[r];
     // every (row, key) pair of the sub-tile allowed: no element mask
     const bool wcut = win && j0 + 32 > p.n_global &&
                       (pos0 < p.n_global || wave_last - j0 >= p.window || j0 + 31 - pos0 >= p.window);
@@ -554,7 +557,18 @@ hipError_t launch_attn_fwd_generic(const void* q_idx, const void* q_val, const v
   p.o = o; p.lse = lse;
   p.Hq = Hq; p.Hkv = Hkv; p.n = n; p.d = d; p.k = k;
   p.causal = causal; p.window = window; p.n_global = n_global;
-  p.scale_log2 = (float)((double)scale * 1.4426950408889634);
+  const float scale_log2 = (float)((double)scale * 1.4426950408889634);
+  p.q_mul = scale_log2;
+  p.s_mul = 1.f;
+  if (vbf16 && vfmt != kValF32) {
+    // raw 16-bit operands: the scores take |scale_log2|.  Its power of two goes to bf16
+    // queries (exact; a product then overflows where that of scaled queries would), its
+    // sign to either kind, and a zero scale as zero queries
+    int e = 0;
+    if (vfmt == kValBF16 && scale_log2 != 0.f) e = std::min(std::max(ilogbf(scale_log2), -126), 127);
+    p.q_mul = scale_log2 == 0.f ? 0.f : copysignf(ldexpf(1.f, e), scale_log2);
+    p.s_mul = scale_log2 == 0.f ? 1.f : ldexpf(fabsf(scale_log2), -e);
+  }
   p.ifmt = ifmt; p.vfmt = vfmt; p.obf16 = obf16;
   p.G = Hq / Hkv;
   p.gs = p.G % 4 == 0 ? 4 : p.G % 2 == 0 ? 2 : 1;

@@ -480,12 +480,14 @@ def test_generic_forward_error_against_64_bits(Hq, Hkv, n, d, k, codes, v_bf16):
         assert e <= 1.25 * b, nm
 
 
-@pytest.mark.parametrize("what", ["v", "keys", "queries", "raised maximum"])
+@pytest.mark.parametrize("what", ["v", "keys", "queries", "raised maximum", "bf16 product", "scale 0",
+                                  "negative scale"])
 @pytest.mark.parametrize("d", [96, 200])
 def test_generic_forward_extreme_magnitudes(what, d):
     """Values and products at the ends of the float32 range, where float32 arithmetic
     stays finite: the largest float32 as V or a code value (past the largest bf16), a
-    running maximum raised by less than 2^8 under V of 2^121."""
+    running maximum raised by less than 2^8 under V of 2^121, products of bf16 codes
+    that only the scale brings back into range."""
     n, k, scale, causal, vdt, cdt = 96, 4, _LN2, True, torch.float32, torch.float32
     rng = np.random.default_rng(d)
     qi = np.tile(np.arange(k), (1, 1, n, 1)); ki = qi.copy()
@@ -505,6 +507,15 @@ def test_generic_forward_extreme_magnitudes(what, d):
         qv[..., 0] = 1.0
         kv[0, 0, 64, 0] = 7.0
         v[...] = 1.5 * 2.0 ** 121
+    else:
+        cdt, vdt = torch.bfloat16, torch.bfloat16
+        qv[...] = 0; kv[...] = 0
+        qv[..., 0] = 2.0 ** 65
+        kv[0, 0, :, 0] = np.where(np.arange(n) % 7, -1.0, 1.0) * 2.0 ** 65
+        kv[0, 0, ::7, 0] *= 1.0 + np.arange(len(kv[0, 0, ::7, 0]))[::-1] / 16  # key 0 the largest
+        scale = {"bf16 product": 2.0 ** -6, "scale 0": 0.0, "negative scale": -2.0 ** -6}[what]
+        if what == "negative scale":
+            qv = -qv
     ti, tv = torch.from_numpy(qi).int().to(DEV), torch.from_numpy(qv).to(cdt).to(DEV)
     tki, tkv = torch.from_numpy(ki).int().to(DEV), torch.from_numpy(kv).to(cdt).to(DEV)
     tvv = torch.from_numpy(v).to(vdt).to(DEV)
