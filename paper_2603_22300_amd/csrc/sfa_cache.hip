@@ -47,12 +47,12 @@ __device__ __forceinline__ int32_t advanced_len(const int32_t* seq_len, const in
 // values in and in the cache, as compile-time constants (the stores then
 // carry no format dispatch); else the formats are read from the arguments.
 // Q8: the 8-bit cache (index format from the arguments).
-// STEP (a few new tokens per sequence, as a generation step appends): one
+// STEP (a new token or two per sequence, as a generation step appends): one
 // workgroup per sequence, wavefronts over its KV heads, each with all the
 // head's tokens; when every wavefront is done the workgroup advances the
 // sequence's length itself.  A step is bound by its launches, and this takes
-// the second one out (12 sequences x 8 heads, 8-bit cache, append and decode of
-// one token, the same lengths: 55.2 -> 54.0 us together with a shorter host path).
+// the second one out (append_step; 12 sequences x 8 heads, 8-bit cache, append and
+// decode of one token: 55.2 -> 54.0 us together with a shorter host path).
 template <int E, bool COMMON, bool Q8, bool STEP>
 __global__ __launch_bounds__(STEP ? 512 : 256) void sfa_kv_append_kernel(AppendArgs a) {
   static_assert(!(COMMON && Q8), "the 8-bit cache has its own formats");
@@ -192,9 +192,14 @@ __global__ void sfa_kv_advance_kernel(int32_t* seq_len, const int32_t* n_new, in
   if (b < B) seq_len[b] = advanced_len(seq_len, n_new, b, T, cap);
 }
 
+// The formats of a COMMON kernel.
+static bool common_formats(const AppendArgs& a) {
+  return !a.q8 && a.ifmt == kIdxI16 && a.vfmt == kValBF16 && a.vin_bf16 && a.vc_bf16;
+}
+
 template <bool STEP>
 static hipError_t launch_append(const AppendArgs& a, dim3 grid, dim3 block, hipStream_t stream) {
-  const bool common = !a.q8 && a.ifmt == kIdxI16 && a.vfmt == kValBF16 && a.vin_bf16 && a.vc_bf16;
+  const bool common = common_formats(a);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, stream, a); };
   if (a.q8) {
     if (a.d <= 64) go(sfa_kv_append_kernel<1, false, true, STEP>);
@@ -210,12 +215,24 @@ static hipError_t launch_append(const AppendArgs& a, dim3 grid, dim3 block, hipS
   return hipGetLastError();
 }
 
-// Most new tokens per sequence of the one-launch append.
-constexpr int kStepTokens = 4;
+// Whether an append runs in one launch (STEP).  Its wavefronts take their rows in
+// turn, a row's chain each about as long as the launch that it saves: measured in
+// graph replays, with a copy of the lengths, two launches -> one, d = 128, k = 16:
+//   one row each (T = 1, up to 8 KV heads), any format: bf16 cache 12 x 8 heads
+//     6.4 -> 5.0 us, 256 x 8 8.2 -> 5.5; 8-bit 7.2 -> 6.0, 9.6 -> 6.6; d = 256 8-bit 8.4 -> 7.4
+//   two rows: bf16 cache 12 x 8 heads T = 2 6.4 -> 6.2, 12 x 16 T = 1 6.5 -> 6.5,
+//     256 x 16 10.6 -> 7.1; but 8-bit 7.2 -> 7.5, float32 7.0 -> 7.2, bf16 at d = 256 7.3 -> 7.4
+//   two or three rows of 256 sequences, whose second launch is the longer one: 256 x 8
+//     T = 3, bf16 at d = 256 11.1 -> 9.6, float32 11.1 -> 9.4, 8-bit 11.5 -> 10.3
+//   four rows: bf16 6.6 -> 8.1, 8-bit 7.3 -> 11.0; 32 heads T = 1 6.5 -> 8.9
+// The workgroups' threads, up to 512 each, have to fit a launch's 32-bit count.
+static bool append_step(const AppendArgs& a) {
+  const int64_t rows = (int64_t)a.T * ((a.Hkv + 7) / 8);
+  return rows > 0 && rows <= (a.B >= 256 ? 3 : common_formats(a) && a.d <= 128 ? 2 : 1) && a.B <= 65535;
+}
 
 hipError_t launch_kv_append(const AppendArgs& a, hipStream_t stream) {
-  if (a.T > 0 && a.T <= kStepTokens)
-    return launch_append<true>(a, dim3(a.B), dim3(64 * (a.Hkv < 8 ? a.Hkv : 8)), stream);
+  if (append_step(a)) return launch_append<true>(a, dim3(a.B), dim3(64 * (a.Hkv < 8 ? a.Hkv : 8)), stream);
   if (a.T > 0) {
     // about 2048 workgroups of 4 waves (8 per compute unit) over the pairs
     const int pairs = a.B * a.Hkv;

@@ -93,6 +93,68 @@ def test_append_capacity_and_pages_outside_the_pool():
     _assert_pool_equal(gpu, ref, "append at capacity")
 
 
+@pytest.mark.parametrize("Hkv,T,d,common", [
+    (1, 1, 128, True), (8, 1, 64, True), (8, 1, 256, False),   # one row per wavefront
+    (9, 1, 128, True), (16, 1, 64, True), (8, 2, 128, True),   # two
+    (9, 1, 128, False), (17, 1, 128, True), (8, 2, 200, True), (2, 3, 64, True), (3, 4, 128, True),  # two launches
+])
+@pytest.mark.parametrize("paged", [True, False])
+def test_append_step(Hkv, T, d, common, paged):
+    """Appends of a few new tokens, on both sides of the line of the one-launch form:
+    a sequence in its first page, one across a page's end, a full one, one with
+    nothing to append and one whose page lies outside the pool."""
+    B, k, P, max_pages = 5, 8, 16, 2
+    idx_dt, val_dt, v_dt = (torch.int16, torch.bfloat16, torch.bfloat16) if common else \
+        (torch.int32, torch.float32, torch.float32)
+    num_pages = B * max_pages if paged else B
+    table_np = np.random.default_rng(T).permutation(num_pages).reshape(B, max_pages).astype(np.int32) if paged else None
+    if paged:
+        table_np[4, 0] = num_pages + 2
+    gpu, ref = _pool(num_pages, Hkv, P if paged else P * max_pages, k, d, idx_dt, val_dt, v_dt)
+    lens_np = np.array([3, 15, 32, 7, 9], dtype=np.int64)
+    n_np = np.array([T, T, T, 0, T], dtype=np.int32)
+    for step in range(2):
+        lens = torch.tensor(lens_np, dtype=torch.int32, device=DEV)
+        kn = si.normal((B, Hkv, T, d), step, "k_new", device=DEV)
+        vn = si.normal((B, Hkv, T, d), step, "v_new", device=DEV).to(v_dt)
+        sfa.sfa_kv_append(kn, vn, lens, *gpu, k=k, n_new=torch.from_numpy(n_np).to(DEV) if step == 0 else None,
+                          block_table=torch.from_numpy(table_np).to(DEV) if paged else None)
+        torch.cuda.synchronize()
+        lens_np = oracle.kv_append(*ref, kn.cpu().numpy(), np_vals(vn), lens_np, k, table_np,
+                                   P if paged else None, n_np if step == 0 else None)
+        assert lens.cpu().numpy().tolist() == lens_np.tolist()
+        _assert_pool_equal(gpu, ref, f"append step {step}")
+
+
+def test_append_step_many_sequences():
+    """256 sequences, three rows to a wavefront: one launch; every sequence as by itself."""
+    B, Hkv, T, d, k, P = 256, 4, 3, 64, 8, 8
+    kn = si.normal((B, Hkv, T, d), 1, "k_new", device=DEV)
+    vn = si.normal((B, Hkv, T, d), 1, "v_new", device=DEV).to(torch.bfloat16)
+    lens_np = np.random.default_rng(1).integers(0, P + 1, B)
+    gpu, ref = _pool(B, Hkv, P, k, d, torch.int16, torch.bfloat16, torch.bfloat16)
+    lens = torch.tensor(lens_np, dtype=torch.int32, device=DEV)
+    sfa.sfa_kv_append(kn, vn, lens, *gpu, k=k)
+    torch.cuda.synchronize()
+    want = oracle.kv_append(*ref, kn.cpu().numpy(), np_vals(vn), lens_np, k)
+    assert lens.cpu().numpy().tolist() == want.tolist()
+    _assert_pool_equal(gpu, ref, "append of 256 sequences")
+
+
+def test_append_more_sequences_than_a_launch_has_threads_for():
+    """2^23 sequences of 8 KV heads: workgroups of 512 threads for each would pass
+    the 2^32 threads of a launch."""
+    B, Hkv = 1 << 23, 8
+    kn = torch.arange(1, B * Hkv + 1, device=DEV, dtype=torch.float32).reshape(B, Hkv, 1, 1)
+    vn = kn.to(torch.bfloat16)
+    ci = torch.full((B, Hkv, 1, 1), -1, dtype=torch.int16, device=DEV)
+    cv, vc = torch.zeros_like(vn), torch.zeros_like(vn)
+    lens = torch.zeros(B, dtype=torch.int32, device=DEV)
+    sfa.sfa_kv_append(kn, vn, lens, ci, cv, vc, k=1)
+    torch.cuda.synchronize()
+    assert (ci == 0).all() and torch.equal(cv, vn) and torch.equal(vc, vn) and (lens == 1).all()
+
+
 def _paged_copy(ci, cv, vc, P, rng, spare=3):
     """Scatter a contiguous cache [B, Hkv, Lmax, ...] into a shuffled page pool."""
     B, Hkv, Lmax = ci.shape[:3]

@@ -74,6 +74,43 @@ def test_append_q8_bit_exact(B, Hkv, T, Lmax, d, k, seq, v_bf16, idx_dtype):
           "(indices, int8 codes, scales)", flush=True)
 
 
+@pytest.mark.parametrize("Hkv,T,d,k,v_bf16", [
+    (1, 1, 128, 16, True), (8, 1, 64, 8, True), (5, 1, 256, 32, False),  # one launch
+    (9, 1, 128, 16, True), (8, 2, 128, 16, True), (12, 1, 64, 8, False), (2, 4, 128, 32, True),  # two
+])
+@pytest.mark.parametrize("paged", [True, False])
+def test_append_step_q8_bit_exact(Hkv, T, d, k, v_bf16, paged):
+    """A generation step's append to the 8-bit cache, on both sides of the line of
+    the one-launch form: a sequence in its first page, one across a page's end, a full
+    one, one with nothing to append and one whose page lies outside the pool."""
+    B, P, max_pages = 5, 16, 2
+    cap = P * max_pages
+    lens_np, n_np = np.array([3, 15, cap, 7, 9]), np.array([T, T, T, 0, T], dtype=np.int32)
+    kn = si.normal((B, Hkv, T, d), d + T, "k_new", device=DEV)
+    vn = si.normal((B, Hkv, T, d), d + T, "v_new", device=DEV).to(torch.bfloat16 if v_bf16 else torch.float32)
+    cache = _q8_cache(B, Hkv, P if paged else cap, d, k, pages=B * max_pages if paged else None)
+    untouched = [x.cpu().numpy() for x in _q8_cache(B, Hkv, cap, d, k)]
+    want = [x.copy() for x in untouched]
+    new = oracle.kv_append_q8(*want, kn.cpu().numpy(), np_vals(vn), lens_np, k, n_new=n_np)
+    table = None
+    if paged:
+        table_np = np.random.default_rng(T).permutation(B * max_pages).reshape(B, max_pages).astype(np.int32)
+        lost = int(table_np[4, 0])
+        table_np[4, 0] = B * max_pages + 2
+        table = torch.from_numpy(table_np).to(DEV)
+    lens = torch.tensor(lens_np, dtype=torch.int32, device=DEV)
+    sfa.sfa_kv_append_q8(kn, vn, lens, *cache, k=k, block_table=table, n_new=torch.from_numpy(n_np).to(DEV))
+    torch.cuda.synchronize()
+    assert lens.cpu().numpy().tolist() == new.tolist()
+    for got, w, u in zip(cache, want, untouched):
+        got = got.cpu().numpy()
+        if paged:  # the pool, by sequence; the page that no table entry names stays as it was
+            table_np[4, 0] = lost
+            got = got[table_np].swapaxes(1, 2).reshape(w.shape)
+            w[4, :, :P] = u[4, :, :P]
+        assert np.array_equal(got.view(np.uint8), w.view(np.uint8))
+
+
 def _decode_case(B, Hq, Hkv, Lmax, d, k, seq, seed, window=0, n_global=0, dense_q=False,
                  paged=False):
     kn = si.normal((B, Hkv, Lmax, d), seed, "k", device=DEV)
