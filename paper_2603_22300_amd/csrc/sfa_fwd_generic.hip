@@ -38,6 +38,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "sfa_device.h"
@@ -520,12 +521,19 @@ __global__ __launch_bounds__(Ge::NT) void sfa_fwd_generic_kernel(GenParams p) {
 
 template <class Ge>
 hipError_t launch_gen(GenParams p, int B, hipStream_t stream) {
-  // once per instantiation
-  static const hipError_t configured =
-      Ge::LDS > 65536 ? hipFuncSetAttribute((const void*)sfa_fwd_generic_kernel<Ge>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, Ge::LDS)
-                      : hipSuccess;
-  if (configured != hipSuccess) return configured;
+  if (Ge::LDS > 65536) {
+    // once per device and instantiation (a bit per device; past the 64th on each call)
+    static std::atomic<uint64_t> configured{0};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+    if (e == hipSuccess && !(configured.load(std::memory_order_relaxed) & bit)) {
+      e = hipFuncSetAttribute((const void*)sfa_fwd_generic_kernel<Ge>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, Ge::LDS);
+      if (e == hipSuccess) configured.fetch_or(bit, std::memory_order_relaxed);
+    }
+    if (e != hipSuccess) return e;
+  }
   p.BR = Ge::R / p.gs;
   p.nqb = (p.n + p.BR - 1) / p.BR;
   hipLaunchKernelGGL((sfa_fwd_generic_kernel<Ge>), dim3(p.nqb, B * p.Hq / p.gs), dim3(Ge::NT),

@@ -536,3 +536,15 @@ def test_generic_forward_extreme_magnitudes(what, d):
     assert (np.abs(wide(o)[0, 0] - O) <= TOL_O_F32 * mag).all()
     # float32 scores: 2^-23 of their size beside the bound of ordinary ones
     assert (np.abs(wide(lse)[0, 0] - L) <= 1e-5 + 2.0 ** -22 * np.abs(L)).all()
+
+
+@pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs two GPUs in one process")
+def test_generic_forward_on_a_second_device():
+    """The general kernel's LDS limit is set on every device that it runs on."""
+    q, kk, v = si.dense_qkv(1, 3, 1, 200, 128, 5, v_dtype=torch.bfloat16, device=DEV)
+    (qi, qv), (ki, kv) = _gpu_codes(q, 16), _gpu_codes(kk, 16)
+    o = []
+    for dev in range(2):
+        with torch.cuda.device(dev):
+            o.append(sfa.sfa_attn_fwd(*(x.to(f"cuda:{dev}") for x in (qi, qv, ki, kv, v)))[0].cpu())
+    assert torch.equal(o[0], o[1])
