@@ -306,7 +306,8 @@ sfa_status sfa_attn_decode(const void* q_idx, const void* q_val,
  * callers that cannot allocate device memory around the call (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc).
  *
- * Same arguments, definitions, kernels and results (bit for bit) as
+ * Same arguments, definitions, kernels and results (bit for bit, as with a
+ * workspace of sfa_attn_decode_workspace bytes) as
  * sfa_attn_decode, minus ws / ws_bytes.  The partial (max, sum, output)
  * triples of the context chunks go to a static device scratch array of the
  * library, SFA_DECODE_NOALLOC_MAX_BYTES per GPU, which each GPU the library
@@ -319,8 +320,7 @@ sfa_status sfa_attn_decode(const void* q_idx, const void* q_val,
  * Errors: as sfa_attn_decode; SFA_ENOSPC when the partials of 4096-key
  * chunks exceed SFA_DECODE_NOALLOC_MAX_BYTES (at d = 128: B * Hq *
  * ceil(Lmax / 4096) <= 64,527 query-head chunks, e.g. 64 sequences x 32
- * heads x 64K keys; a finer split that would not fit is not made, by either
- * entry point); SFA_EHIP if the scratch address cannot be looked up.
+ * heads x 64K keys; a finer split always fits); SFA_EHIP if the scratch address cannot be looked up.
  */
 #define SFA_DECODE_NOALLOC_MAX_BYTES ((size_t)32 << 20)
 sfa_status sfa_attn_decode_noalloc(const void* q_idx, const void* q_val,
@@ -423,8 +423,9 @@ sfa_status sfa_kv_append(const float* k_new, const void* v_new, const int32_t* n
  *                 sfa_attn_decode, with the
  *                 workspace sized by
  *                 sfa_attn_decode_workspace(B, Hq, max_pages * page_size, d).
- * The result equals sfa_attn_decode on the gathered contiguous cache (same
- * chunking and summation order, hence the same bits).
+ * The result equals sfa_attn_decode on the gathered contiguous cache, whatever
+ * the two capacities (same chunking and summation order, hence the same bits, with
+ * workspaces of sfa_attn_decode_workspace bytes).
  * Limits: as sfa_attn_decode; max_pages * page_size <= 2^30.
  * Errors: SFA_EINVAL, SFA_ENOTSUP, SFA_ENOSPC, SFA_EHIP.
  */

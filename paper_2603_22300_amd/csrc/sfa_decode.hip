@@ -1,6 +1,9 @@
 // SFA decode step (App. B, KV-cache attention) on gfx950: launchers of the
 // decode kernel (sfa_decode_kernel.h) for bf16 / float32 V caches, and the
 // merge of the context chunks' partials by their LSE.
+#include <algorithm>
+
+#include "../../include/sfa.h"
 #include "sfa_decode_kernel.h"
 
 namespace sfa {
@@ -8,18 +11,20 @@ namespace sfa {
 // Merge the chunk partials of each (b, h): O = sum_c w_c o_c / sum_c w_c l_c,
 // w_c = 2^(m_c - M), LSE = (M + log2 sum_c w_c l_c) ln 2.  A few KB of
 // dependent loads per row: each wave takes the maximum and the sum with
-// lanes over the chunks, and the workgroup's T / D groups of D threads (thread
-// = dimension) take every group-count-th chunk of the output sum; the groups'
-// sums are added in order.  T = 512 for more than 16 slots, where one group's
-// sum is a long serial chain (64,000 keys of one sequence: 38.0 -> 35.3 us a
-// step), else one group (2048 rows of 1 to 8 chunks: 4 us less).
+// lanes over the chunks.  The output sum (thread = dimension) is kMergeThreads / D
+// sums, each over the chunks of one residue, added in order: by as many groups of
+// threads (T = kMergeThreads; launch_decode_combine), or in turn by one (T = D).  Which
+// of the two runs follows the cache's capacity; the order of the sums, and so the
+// bits, do not.
+constexpr int kMergeThreads = 512;
 template <int D, int T>
 __global__ __launch_bounds__(T) void sfa_decode_combine_kernel(
     const float* __restrict__ ws_m, const float* __restrict__ ws_l, const float* __restrict__ ws_o,
     const int32_t* seq_len, int Hq, int Lmax, int nch, int window, int n_global, int aim, void* o,
     int obf16, float* lse) {
-  constexpr int NG = T / D;
-  __shared__ float part[NG][D];
+  constexpr int NG = kMergeThreads / D;
+  static_assert(T == D || T == kMergeThreads, "one group of threads, or one per sum");
+  __shared__ float part[T == D ? 1 : NG][D];
   const int bh = blockIdx.x;
   const int b = bh / Hq;
   const int dd = threadIdx.x % D, grp = threadIdx.x / D, lane = threadIdx.x & 63;
@@ -31,16 +36,33 @@ __global__ __launch_bounds__(T) void sfa_decode_combine_kernel(
   M = wave_max_dpp(M);
   const float Mu = (M == -INFINITY) ? 0.f : M;
   float lsum = 0.f;
-  for (int c = lane; c < nc; c += 64) lsum += exp2f(ws_m[s0 + c] - Mu) * ws_l[s0 + c];
+  for (int c = lane; c < nc; c += 64) lsum = fmaf(exp2f(ws_m[s0 + c] - Mu), ws_l[s0 + c], lsum);
   lsum = wave_sum(lsum);
   float osum = 0.f;
-#pragma unroll 4
-  for (int c = grp; c < nc; c += NG) osum += exp2f(ws_m[s0 + c] - Mu) * ws_o[(s0 + c) * D + dd];
-  part[grp][dd] = osum;
-  __syncthreads();
-  if (grp != 0) return;
+  if constexpr (T == D) {
+    float os[NG];
 #pragma unroll
-  for (int g = 1; g < NG; ++g) osum += part[g][dd];
+    for (int g = 0; g < NG; ++g) os[g] = 0.f;
+    for (int c0 = 0; c0 < nc; c0 += NG) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {  // (past the last chunk: read, not added)
+        const int c = min(c0 + g, nc - 1);
+        const float x = ws_o[(s0 + c) * D + dd], w = exp2f(ws_m[s0 + c] - Mu);
+        os[g] = c0 + g < nc ? fmaf(w, x, os[g]) : os[g];
+      }
+    }
+    osum = os[0];
+#pragma unroll
+    for (int g = 1; g < NG; ++g) osum += os[g];
+  } else {
+#pragma unroll 4
+    for (int c = grp; c < nc; c += NG) osum = fmaf(exp2f(ws_m[s0 + c] - Mu), ws_o[(s0 + c) * D + dd], osum);
+    part[grp][dd] = osum;
+    __syncthreads();
+    if (grp != 0) return;
+#pragma unroll
+    for (int g = 1; g < NG; ++g) osum += part[g][dd];
+  }
   const float out = lsum > 0.f ? osum / lsum : 0.f;
   if (obf16) ((uint16_t*)o)[(int64_t)bh * D + dd] = (uint16_t)f32_to_bf16_rne(out);
   else ((float*)o)[(int64_t)bh * D + dd] = out;
@@ -55,31 +77,30 @@ size_t decode_workspace_bytes_min(int B, int Hq, int Lmax, int d) {
   return slot_bytes(B, Hq, (size_t)((Lmax + kDecodeChunk - 1) / kDecodeChunk), d);
 }
 
-// Whether a step of these sizes may cut sequences below kDecodeChunk keys, and
-// the bytes of the slots it then needs, for any group (a group of kDecMaxG
-// heads and a window have the largest aim), cache format and token window (two slots more than its
-// span of keys: the global keys' last chunk and the window's first are partly
-// filled).  A step whose slots would fit the allocation-free decode's scratch
-// only in chunks of kDecodeChunk keys keeps those, whatever the caller's
-// workspace, so that both entry points give the same bits.
-static bool fine_bytes(int B, int Hq, int Lmax, int d, size_t* bytes) {
-  const int aim = decode_chunks_aim(B, (Hq + kDecMaxG - 1) / kDecMaxG, true, 1);
-  if (aim == 0) return false;
+// The most partial slots of a step over Lmax keys with that aim, windowed or not: a
+// sequence has at most aim + 2 chunks below kDecodeChunk keys (decode_plan; under a
+// window the global keys' last chunk and the window's first are partly filled), or
+// its whole chunks of kDecodeChunk.
+static int most_slots(int Lmax, int aim) {
   const int fine = Lmax / kDecodeMinChunk + (Lmax % kDecodeMinChunk != 0);
-  *bytes = slot_bytes(B, Hq, (size_t)min(fine, decode_slots(Lmax, aim) + 2), d);
-  return *bytes <= noalloc_scratch_bytes() ||
-         decode_workspace_bytes_min(B, Hq, Lmax, d) > noalloc_scratch_bytes();
+  return aim == 0 ? decode_slots(Lmax, 0) : std::min(fine, std::max(decode_slots(Lmax, 0), aim + 2));
 }
 
+// For any group (a group of kDecMaxG heads and a window have the largest aim),
+// cache format and token window.  A finer cut never needs more than the
+// allocation-free decode's scratch has: B * Hq * (aim + 2) <= 24 * kDecodeTargetWindow.  So
+// that entry point cuts as the others do, and whether a cut is made does not
+// depend on the capacity.
 size_t decode_workspace_bytes(int B, int Hq, int Lmax, int d) {
-  size_t bytes;
-  return fine_bytes(B, Hq, Lmax, d, &bytes) ? bytes : decode_workspace_bytes_min(B, Hq, Lmax, d);
+  static_assert(kDecodeTarget <= kDecodeTargetWindow && kDecodeTargetQ8 <= kDecodeTargetWindow, "largest aim");
+  static_assert((size_t)3 * kDecMaxG * kDecodeTargetWindow * (128 + 2) * sizeof(float) <=
+                    SFA_DECODE_NOALLOC_MAX_BYTES, "a finer cut fits the scratch");
+  if (d != 64 && d != 128) return decode_workspace_bytes_min(B, Hq, Lmax, d);
+  return slot_bytes(B, Hq, most_slots(Lmax, decode_chunks_aim(B, (Hq + kDecMaxG - 1) / kDecMaxG, true, 1)), d);
 }
 
 int decode_aim(int B, int Hq, int Hkv, int Lmax, int d, int window, size_t ws_bytes, bool q8) {
-  size_t bytes;
-  return fine_bytes(B, Hq, Lmax, d, &bytes) && ws_bytes >= bytes
-             ? decode_chunks_aim(B, Hkv, q8, window) : 0;
+  return ws_bytes >= decode_workspace_bytes(B, Hq, Lmax, d) ? decode_chunks_aim(B, Hkv, q8, window) : 0;
 }
 
 template <int D, int G, bool VBF16, int KC8, bool C8>
@@ -126,15 +147,12 @@ DecParams make_dec_params(const DecodeArgs& a) {
   p.G = a.Hq / a.Hkv;
   p.aim = a.aim;
   p.window = a.window; p.n_global = a.n_global;
-  const int fine = a.Lmax / kDecodeMinChunk + (a.Lmax % kDecodeMinChunk != 0);
   const int64_t wspan = (int64_t)a.window + a.n_global;
-  const int full = (a.Lmax + kDecodeChunk - 1) / kDecodeChunk;
   p.nch = decode_slots(a.Lmax, a.aim);
   if (a.window > 0 && wspan < a.Lmax) {
     // a sequence still inside the window, or whose query is a global token,
     // is cut as without one: its length is at most wspan
-    const int w = decode_slots((int)wspan, a.aim) + 2;
-    p.nch = min(w, a.aim == 0 ? full : fine);
+    p.nch = std::min(decode_slots((int)wspan, a.aim) + 2, most_slots(a.Lmax, a.aim));
   }
   const size_t nslot = (size_t)a.B * a.Hq * p.nch;
   p.ws_m = (float*)a.ws;
@@ -156,11 +174,15 @@ hipError_t launch_decode_combine(const DecParams& p, const DecodeArgs& a, hipStr
                        a.seq_len, a.Hq, a.Lmax, p.nch, p.window, p.n_global, p.aim, a.o, a.obf16,
                        a.lse);
   };
+  // Groups of threads where one's sum is a long serial chain (64,000 keys of one
+  // sequence, 63 chunks: 38.0 -> 35.3 us a step; 4000 keys, 16: 14.0 -> 11.2), one group
+  // where the rows fill the chip (2048 rows of 1 to 8 chunks: 4 us less).
+  const bool many = p.nch > 16 || (p.nch > 4 && a.B * a.Hq <= 1024);
   if (a.d == 64) {
-    if (p.nch > 16) go(sfa_decode_combine_kernel<64, 512>, 512);
+    if (many) go(sfa_decode_combine_kernel<64, kMergeThreads>, kMergeThreads);
     else go(sfa_decode_combine_kernel<64, 64>, 64);
   } else {
-    if (p.nch > 16) go(sfa_decode_combine_kernel<128, 512>, 512);
+    if (many) go(sfa_decode_combine_kernel<128, kMergeThreads>, kMergeThreads);
     else go(sfa_decode_combine_kernel<128, 128>, 128);
   }
   return hipGetLastError();

@@ -227,7 +227,7 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
   const int pg0 = PAGED ? (w0 >> p.log2P) : 0;
   if constexpr (PAGED) {
     if (w0 < w1) {
-      // <= 64 (P >= 16; w0 is 1024-aligned, or 64-aligned at a window start)
+      // <= 64 (P >= 16; at most 1024 positions, and w0 is a multiple of 64)
       const int npg = ((w1 - 1) >> p.log2P) - pg0 + 1;
       if (lane < npg) {
         const int pg = p.table[(int64_t)b * p.max_pages + pg0 + lane];

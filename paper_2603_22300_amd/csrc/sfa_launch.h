@@ -88,7 +88,8 @@ constexpr int kDecodeChunk = 4096;
 constexpr int kDecodeMinChunk = 256;
 constexpr int kDecodeTarget = 256, kDecodeTargetQ8 = 1024, kDecodeTargetWindow = 2048;
 // Chunks per (sequence, KV head) that a step over B * Hkv of them aims at.
-// 0 or 1: every chunk has kDecodeChunk keys (B * Hkv alone meets the target).
+// 0: every chunk has kDecodeChunk keys (B * Hkv alone passes the target); 1: the same,
+// but a sequence that fits one smaller chunk has that.
 inline int decode_chunks_aim(int B, int Hkv, bool q8, int window) {
   const int target = window > 0 ? kDecodeTargetWindow : q8 ? kDecodeTargetQ8 : kDecodeTarget;
   return (int)(target / ((int64_t)B * Hkv));

@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -254,6 +255,23 @@ def test_compact_dtypes_accepted_for_codes_only(L):
     assert _fwd(L, o_t=5) == 1
     assert _dec(L, kc_idx_t=4, kc_val_t=5, ws_bytes=1) == 4
     assert _dec(L, v_t=5) == 1
+
+
+def test_decode_workspace_of_a_finer_cut_fits_the_scratch(L):
+    # where the allocation-free decode takes a step in whole chunks, it also holds the
+    # slots of the finest cut: no capacity loses it
+    rng = np.random.default_rng(0)
+    sizes = [(128, 32, Lmax) for Lmax in range(53248, 65537, 1024)] + [(64, 32, 122880), (256, 32, 28672)]
+    sizes += [(int(2 ** rng.uniform(0, 10)), int(2 ** rng.uniform(0, 7)), int(2 ** rng.uniform(4, 20)))
+              for _ in range(20000)]
+    for d in (64, 128):
+        for B, Hq, Lmax in sizes:
+            whole = B * Hq * -(-Lmax // 4096) * (d + 2) * 4
+            need = L.sfa_attn_decode_workspace(B, Hq, Lmax, d)
+            assert need >= whole, (B, Hq, Lmax, d)
+            assert need <= 32 << 20 or whole > 32 << 20, (B, Hq, Lmax, d)
+            # monotonic in the capacity: a larger cache is never cut more coarsely
+            assert need <= L.sfa_attn_decode_workspace(B, Hq, 2 * Lmax, d)
 
 
 def test_decode_noalloc_host_checks(L):

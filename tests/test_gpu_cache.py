@@ -223,6 +223,53 @@ def test_paged_decode(B, Hq, Hkv, Lmax, d, k, P, v_bf16, seq):
         assert torch.isneginf(l_f[torch.from_numpy(~live).to(DEV)]).all()
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L,window,n_global,q8,capacities", [
+    (1, 32, 8, 3000, 0, 0, False, (8192, 16384, 1 << 20)),          # 12 chunks; slots for 16 and more
+    (1, 32, 8, 3000, 0, 0, True, (16384,)),
+    (1, 8, 2, 9000, 700, 5, False, (9088, 65536)),                  # a window
+    (128, 32, 8, 6000, 3000, 4, False, (53248, 57344, 61440, 65536)),  # whole chunks near the scratch's size
+    (128, 32, 8, 4000, 0, 0, True, (53248, 57344, 65536)),
+])
+def test_capacity_does_not_change_the_bits(B, Hq, Hkv, L, window, n_global, q8, capacities):
+    """The same sequences in a tight contiguous cache and through block tables of larger
+    capacities: the same cut and the same order of sums, so the same bits."""
+    d, k, P = 128, 8, 64
+    used = -(-L // P)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    lens = torch.randint(L // 2, L + 1, (B,), generator=g, device=DEV).to(torch.int32)
+    lens[0] = L
+    shape, one = (B * used, Hkv, P), dict(dtype=torch.float32, device=DEV)
+    ci = torch.empty(shape + (k,), dtype=torch.int16, device=DEV)
+    cv = torch.empty(shape + (k,), dtype=torch.bfloat16, device=DEV)
+    vc = torch.empty(shape + (d,), dtype=torch.bfloat16, device=DEV)
+    for b in range(0, B * used, 512):
+        x = torch.randn((min(512, B * used - b),) + shape[1:] + (d,), generator=g, **one)
+        sfa.sfa_topk_encode(x, k, idx=ci[b:b + 512], val=cv[b:b + 512])
+        vc[b:b + 512] = torch.randn(x.shape, generator=g, **one)
+    if q8:
+        cv, vc = (x.clamp(-3, 3).mul(40).to(torch.int8) for x in (cv, vc))
+    ks, vs = (torch.rand(shape, generator=g, **one) / 40 for _ in range(2))
+    q = torch.randn((B, Hq, d), generator=g, **one)
+    kw = dict(seq_len=lens, o_dtype=torch.float32, window=window, n_global=n_global)
+
+    def tight(x):
+        return x.reshape((B, used) + x.shape[1:]).transpose(1, 2).reshape((B, Hkv, used * P) + x.shape[3:])[:, :, :L].contiguous()
+    if q8:
+        want = sfa.sfa_attn_decode_q8(tight(ci), tight(cv), tight(ks), tight(vc), tight(vs), q=q, **kw)
+    else:
+        want = sfa.sfa_attn_decode(*sfa.sfa_topk_encode(q, k), tight(ci), tight(cv), tight(vc), **kw)
+    for cap in capacities:
+        table = torch.zeros((B, cap // P), dtype=torch.int32, device=DEV)
+        table[:, :used] = torch.arange(B * used, device=DEV).reshape(B, used)
+        if q8:
+            got = sfa.sfa_attn_decode_q8(ci, cv, ks, vc, vs, block_table=table, q=q, **kw)
+        else:
+            got = sfa.sfa_attn_decode_paged(ci, cv, vc, table, q=q, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), cap
+
+
 def test_generation_loop():
     """Prefill a paged cache by one append, then decode token by token: each
     step appends the new key and value and decodes the new dense query over the
