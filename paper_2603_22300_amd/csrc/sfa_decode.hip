@@ -154,6 +154,14 @@ DecParams make_dec_params(const DecodeArgs& a) {
     // is cut as without one: its length is at most wspan
     p.nch = std::min(decode_slots((int)wspan, a.aim) + 2, most_slots(a.Lmax, a.aim));
   }
+  // The 8-bit cache's step is bound by its arithmetic, and slots that a sequence does
+  // not have, dispatched among the others, leave compute units with fewer workgroups: by
+  // slot they come last (24 x 8 heads of 16,384 keys, four of five slots in use: 134 ->
+  // 118 us, 117 with four slots; 12 x 8 mixed lengths to 12,000 47.7 -> 41.5).  Not with few
+  // heads, whose workgroups are all resident: there it puts the chunks of one sequence
+  // on one compute unit (8 x 8 mixed lengths to 5000: 17.8 -> 20.7).  Over bf16 caches,
+  // bound by memory, it was up to 2.5% slower.
+  p.by_slot = a.kc_scale != nullptr && a.B * a.Hkv >= 96 && p.nch <= 65535;
   const size_t nslot = (size_t)a.B * a.Hq * p.nch;
   p.ws_m = (float*)a.ws;
   p.ws_l = p.ws_m + nslot;

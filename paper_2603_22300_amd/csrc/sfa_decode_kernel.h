@@ -59,6 +59,7 @@ struct DecParams {
   int G;    // query heads per KV head (the kernel's G is the next power of two)
   int nch;  // partial slots per (b, h), and chunks of the grid
   int aim;  // chunks per sequence aimed at (decode_chunks_aim)
+  int by_slot;  // 8-bit cache: grid (B * Hkv, slots) instead of (slots, B * Hkv)
   float scale_log2;
   int qifmt, qvfmt, kifmt, kvfmt;
   const float* q_dense;   // [B, Hq, D] or null (then q_idx / q_val)
@@ -150,10 +151,11 @@ __global__ __launch_bounds__(kDecThreads) void sfa_decode_kernel(DecParams p) {
   // rotates with the head, so that the slots past a short sequence's end, or
   // outside a window's keys, leave no XCD idle (64 x 16K keys under a
   // 4096-key window in four slots, three in use: 257 us unrotated against
-  // 221 in the same chunks).
-  const int bh = blockIdx.y;
-  unsigned slot_u = blockIdx.x;
-  if (gridDim.x % 2 == 0) slot_u = (slot_u + (unsigned)bh + ((unsigned)bh >> 2)) % gridDim.x;
+  // 221 in the same chunks).  by_slot: the grid's other order instead.
+  const bool by_slot = Q8 && p.by_slot;
+  const int bh = by_slot ? blockIdx.x : blockIdx.y;
+  unsigned slot_u = by_slot ? blockIdx.y : blockIdx.x;
+  if (!by_slot && gridDim.x % 2 == 0) slot_u = (slot_u + (unsigned)bh + ((unsigned)bh >> 2)) % gridDim.x;
   const int slot = (int)slot_u;
   const int b = bh / p.Hkv, hkv = bh - b * p.Hkv;
   const int L = seq_len_of(p.seq_len, b, p.Lmax);

@@ -12,7 +12,7 @@ namespace {
 
 template <int D, int G, int KC8>
 void launch_q8_t(const DecParams& p, int B, hipStream_t stream) {
-  const dim3 grid(p.nch, B * p.Hkv), block(kDecThreads);
+  const dim3 grid = p.by_slot ? dim3(B * p.Hkv, p.nch) : dim3(p.nch, B * p.Hkv), block(kDecThreads);
   if (p.table)
     hipLaunchKernelGGL((sfa_decode_kernel<D, G, false, KC8, false, true, true>), grid, block, 0,
                        stream, p);
