@@ -203,6 +203,28 @@ constexpr float kBoundMax = 15.f;
 constexpr uint16_t kHandBack16 = 0x7fa5u;
 constexpr uint32_t kHandBack32 = 0x7fa5a5a5u;
 
+// Code element, within its KV head of n keys, that a lane loads for the tile from
+// key j0 on: entry off = row * k + term of the tile, or for a lane without one (row
+// < 0, off the last of its wavefront's rows) any that exists.  Past the last key it
+// is one of that key's.
+__host__ __device__ constexpr uint32_t tile_code(int j0, int n, int k, int row, int off) {
+  if (j0 + kBC <= n) return (uint32_t)(j0 * k + off);
+  const int r = row < 0 ? 0 : row;
+  const int j = j0 + r < n ? j0 + r : n - 1;
+  return (uint32_t)(j * k + (row < 0 ? 0 : off - r * k));
+}
+constexpr bool tile_codes_exist() {
+  for (int n : {1, 64, 65, 127})
+    for (int k : {1, 8, 33})
+      for (int j0 = 0; j0 < n + kBC; j0 += kBC)
+        for (int row = 0; row < kBC; ++row)
+          if (tile_code(j0, n, k, row, row * k + k - 1) >= (uint32_t)(n * k) ||
+              tile_code(j0, n, k, -1, row * k + k - 1) >= (uint32_t)(n * k))
+            return false;
+  return true;
+}
+static_assert(tile_codes_exist(), "no code is read past the last key");
+
 // One workgroup: query block qb of (batch, KV head) bh.
 // SAFE (bf16 V only): V is staged as bf16 and P.V uses P = Ph + Pl on the
 // bf16 MFMA, every tile on the generic path; the code values are split into
@@ -481,15 +503,7 @@ __device__ __forceinline__ void fwd_block(const FwdParams& p, const int qb, cons
     const bool full = j0 + kBC <= n;
     uint32_t ge[KEL];  // code element within this KV head
 #pragma unroll
-    for (int r = 0; r < KEL; ++r) {
-      if (full) {
-        ge[r] = (uint32_t)(j0 * k + k_off[r]);
-      } else {
-        const int row = k_row[r] < 0 ? 0 : k_row[r];
-        const int j = min(j0 + row, n - 1);
-        ge[r] = (uint32_t)(j * k + (k_off[r] - row * k));
-      }
-    }
+    for (int r = 0; r < KEL; ++r) ge[r] = tile_code(j0, n, k, k_row[r], k_off[r]);
     if (p.ifmt == kIdxI16) {
 #pragma unroll
       for (int r = 0; r < KEL; ++r) kf[r] = *(const int16_t*)(kidx_b + ge[r] * 2u);
