@@ -204,14 +204,14 @@ constexpr uint16_t kHandBack16 = 0x7fa5u;
 constexpr uint32_t kHandBack32 = 0x7fa5a5a5u;
 
 // Code element, within its KV head of n keys, that a lane loads for the tile from
-// key j0 on: entry off = row * k + term of the tile, or for a lane without one (row
-// < 0, off the last of its wavefront's rows) any that exists.  Past the last key it
-// is one of that key's.
+// key j0 on: entry off = row * k + term of the tile, past the last key one of that
+// key's.  A lane without an entry has row -1 and off kNoCode, row 0's first.
+constexpr int kNoCode = 0;
 __host__ __device__ constexpr uint32_t tile_code(int j0, int n, int k, int row, int off) {
   if (j0 + kBC <= n) return (uint32_t)(j0 * k + off);
   const int r = row < 0 ? 0 : row;
   const int j = j0 + r < n ? j0 + r : n - 1;
-  return (uint32_t)(j * k + (row < 0 ? 0 : off - r * k));
+  return (uint32_t)(j * k + (off - r * k));
 }
 constexpr bool tile_codes_exist() {
   for (int n : {1, 64, 65, 127})
@@ -219,7 +219,7 @@ constexpr bool tile_codes_exist() {
       for (int j0 = 0; j0 < n + kBC; j0 += kBC)
         for (int row = 0; row < kBC; ++row)
           if (tile_code(j0, n, k, row, row * k + k - 1) >= (uint32_t)(n * k) ||
-              tile_code(j0, n, k, -1, row * k + k - 1) >= (uint32_t)(n * k))
+              tile_code(j0, n, k, -1, kNoCode) >= (uint32_t)(n * k))
             return false;
   return true;
 }
@@ -485,7 +485,7 @@ __device__ __forceinline__ void fwd_block(const FwdParams& p, const int qb, cons
     el = ok ? el : KW * k - 1;
     const int cl = (int)(((float)el + 0.5f) * p.inv_k);
     k_row[r] = ok ? wave * KW + cl : -1;
-    k_off[r] = (wave * KW + cl) * k + (el - cl * k);
+    k_off[r] = ok ? (wave * KW + cl) * k + (el - cl * k) : kNoCode;
   }
   int kf[KEL];
   float kx[KEL];
