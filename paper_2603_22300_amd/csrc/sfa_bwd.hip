@@ -54,7 +54,11 @@ constexpr int kNWQ = 8;        // dq: wavefronts per workgroup (two per SIMD)
 // d = 128 where eight waves make fewer than 512 workgroups: 2 x 8 heads, n =
 // 1000, whole backward 226 -> 209 us; 32 over 8 heads, n = 2000, 1102 -> 1086.
 // The register cap is stated: without it the compiler kept the accumulators in
-// AGPRs and moved them to and from VGPRs every tile.
+// AGPRs and moved them to and from VGPRs every tile.  At d = 64 with float32 dO the
+// cap costs 4 to 6 spilled registers, and four waves are still the faster ones or within
+// 2% (whole backward, float32 V and O, eight waves against four: 8 heads, n = 333 61
+// and 59 us; 2 x 8, n = 1000 136 and 124; 32 over 8, n = 8192 2950 and 2990; 8 heads,
+// non-causal n = 10,000 2721 and 2515).
 constexpr int kNWQs = 4;
 constexpr float kLog2e = 1.44269504088896340736f;
 
@@ -1261,30 +1265,34 @@ hipError_t launch_d(BwdParams p, int B, hipStream_t stream) {
     if (p.nsplit > 1)
       hipLaunchKernelGGL(sfa_bwd_split_sum_kernel, dim3(kNWF * kT / 16, B * p.Hkv), dim3(256), 0, stream, p, D);
     return hipGetLastError();
-  }
-  // The sweep split two ways where blocks of 256 keys (one workgroup per
-  // compute unit, 256 at a time) leave compute units idle.  Causal blocks differ in
-  // length, so the longest ones set the time until there are many (one way
-  // against two, 32 over 8 heads: n = 8192, 256 blocks: 5.16 and 3.58 ms;
-  // 10,000, 320: 6.84 and 5.64; 12,288, 384: 8.94 and 8.66; 16,384, 512: 13.1 and
-  // 13.9).  Non-causal ones are alike and count in whole passes over the chip, a
-  // pass of half blocks at a little over half the time (8 heads: n = 8192, 256
-  // blocks: 1.69 and 1.78 ms; 12,000, 376: 4.37 and 3.97; 12,800, 400: 4.99 and
-  // 5.36).  (Not under a token window, whose split sweep is of a 256-key block.)
-  const long long nb = (long long)((p.n + kNW * kT - 1) / (kNW * kT)) * B * p.Hkv;
-  const bool two_ways = p.window == 0 && (p.causal ? nb <= 384 : nb <= 128 || (nb > 256 && nb <= 384));
-  hipError_t ek = hipSuccess;
-  if (two_ways) {
-    ek = launch_dkv<D, VEX, OEX, CEX, kDV, 2>(p, B, pers, stream);
-    if (ek == hipSuccess) ek = launch_dkv<D, VEX, OEX, CEX, kDK, 2>(p, B, pers, stream);
   } else {
-    ek = launch_dkv<D, VEX, OEX, CEX, kDV, 1>(p, B, pers, stream);
-    if (ek == hipSuccess) ek = launch_dkv<D, VEX, OEX, CEX, kDK, 1>(p, B, pers, stream);
+    // The sweep split two ways where blocks of 256 keys (one workgroup per
+    // compute unit, 256 at a time) leave compute units idle.  Causal blocks differ in
+    // length, so the longest ones set the time until there are many (one way
+    // against two, d = 128, bf16 dO, 32 over 8 heads: n = 8192, 256 blocks: 5.16 and 3.58
+    // ms; 10,000, 320: 6.84 and 5.64; 12,288, 384: 8.94 and 8.66; 16,384, 512: 13.1 and
+    // 13.9).  Non-causal ones are alike and count in whole passes over the chip, a
+    // pass of half blocks at a little over half the time (8 heads: n = 8192, 256
+    // blocks: 1.69 and 1.78 ms; 12,000, 376: 4.37 and 3.97; 12,800, 400: 4.99 and
+    // 5.36).  d = 64 with float32 V and O gains the same: causal n = 2000, 64 blocks: 0.86
+    // and 0.53; 8192: 4.01 and 2.99; 12,288: 7.19 and 6.44; non-causal 10,000, 320: 2.65 and
+    // 2.52; 12,000: 3.21 and 2.96.  (Not under a token window, whose split sweep is of a
+    // 256-key block.)
+    const long long nb = (long long)((p.n + kNW * kT - 1) / (kNW * kT)) * B * p.Hkv;
+    const bool two_ways = p.window == 0 && (p.causal ? nb <= 384 : nb <= 128 || (nb > 256 && nb <= 384));
+    hipError_t ek = hipSuccess;
+    if (two_ways) {
+      ek = launch_dkv<D, VEX, OEX, CEX, kDV, 2>(p, B, pers, stream);
+      if (ek == hipSuccess) ek = launch_dkv<D, VEX, OEX, CEX, kDK, 2>(p, B, pers, stream);
+    } else {
+      ek = launch_dkv<D, VEX, OEX, CEX, kDV, 1>(p, B, pers, stream);
+      if (ek == hipSuccess) ek = launch_dkv<D, VEX, OEX, CEX, kDK, 1>(p, B, pers, stream);
+    }
+    if (ek != hipSuccess) return ek;
+    if (p.nsplit > 1)
+      hipLaunchKernelGGL(sfa_bwd_split_sum_kernel, dim3(kNW * kT / 16, B * p.Hkv), dim3(256), 0, stream, p, D);
+    return hipGetLastError();
   }
-  if (ek != hipSuccess) return ek;
-  if (p.nsplit > 1)
-    hipLaunchKernelGGL(sfa_bwd_split_sum_kernel, dim3(kNW * kT / 16, B * p.Hkv), dim3(256), 0, stream, p, D);
-  return hipGetLastError();
 }
 
 }  // namespace
