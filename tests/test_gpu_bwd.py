@@ -264,8 +264,9 @@ def test_qwen3_32k_full_size_sampled():
 @pytest.mark.parametrize(
     "B,Hq,Hkv,n,d,k,causal,bf16,win,ng",
     [
-        (2, 16, 8, 4500, 128, 16, True, True, 0, 0),    # dq: 3 rows of blocks per XCD, dk / dv: 2
-        (1, 8, 8, 9000, 64, 8, False, False, 0, 0),     # G = 1, non-causal, float32 V, O and dO
+        (2, 16, 8, 4500, 128, 16, True, True, 0, 0),    # two-way sweep in blocks of 128 keys: 3 rows per XCD
+        (1, 8, 8, 9000, 64, 8, False, False, 0, 0),     # two ways, G = 1, non-causal, float32 V, O and dO
+        (2, 8, 8, 6300, 128, 8, True, False, 0, 0),     # 400 blocks of 256 keys: one way, float32 V, O and dO
         (1, 16, 8, 9000, 128, 16, False, True, 700, 3),  # token window: one workgroup per block
     ])
 def test_persistent_grid_sampled(B, Hq, Hkv, n, d, k, causal, bf16, win, ng):
@@ -353,3 +354,23 @@ def test_two_way_sweep(B, Hq, Hkv, n, causal, v_bf16, o_bf16):
     """Few key blocks at d = 128: the dK and dV workgroups split their sweep two
     ways and add the two sums.  The last two cases lie past the rule's lines."""
     _run(B, Hq, Hkv, n, 128, 16, causal, v_bf16, seed=n + Hq, o_bf16=o_bf16)
+
+
+def test_more_heads_than_one_prepass_launch():
+    """Query and key heads past 65,535 in all: the images are built in two launches.
+    Each half of the batch by itself has one, and gives the same bits."""
+    B, Hq, Hkv, n, d, k = 11000, 4, 2, 5, 64, 2
+    g = torch.Generator(device=DEV)
+    g.manual_seed(1)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device=DEV)
+    qi, qv = sfa.sfa_topk_encode(normal(B, Hq, n, d), k)
+    ki, kv = sfa.sfa_topk_encode(normal(B, Hkv, n, d), k)
+    v, do = normal(B, Hkv, n, d).to(torch.bfloat16), normal(B, Hq, n, d).to(torch.bfloat16)
+    o, lse = sfa.sfa_attn_fwd(qi, qv, ki, kv, v)
+    x = (qi, qv, ki, kv, v, o, lse, do)
+    whole = sfa.sfa_attn_bwd(*x)
+    halves = [sfa.sfa_attn_bwd(*(t[a:a + B // 2].contiguous() for t in x)) for a in (0, B // 2)]
+    for w, a, b in zip(whole, *halves):
+        assert torch.equal(w, torch.cat([a, b]))

@@ -85,6 +85,37 @@ def test_group_not_power_of_two(B, Hq, Hkv, Lmax, d, k, v_bf16, seq):
     _case(B, Hq, Hkv, Lmax, d, k, v_bf16, seq, seed=Hq + Lmax)
 
 
+@pytest.mark.parametrize("d,k,v_bf16", [(128, 16, True), (64, 8, False)])
+def test_group_of_three_unaligned_cache(d, k, v_bf16):
+    """A group that is not a power of two over cache arrays off a 16-byte boundary runs
+    the float32 decode, contiguous and paged: float32 results as from aligned arrays."""
+    B, Hq, Hkv, L, P = 2, 6, 2, 4500, 16
+    pages = -(-L // P)
+    shape = (B * pages, Hkv, P)
+    ci, cv = sfa.sfa_topk_encode(si.normal(shape + (d,), d, "k", device=DEV), k, idx_dtype=torch.int16,
+                                 val_dtype=torch.bfloat16)
+    vc = si.normal(shape + (d,), d, "v", device=DEV).to(torch.bfloat16 if v_bf16 else torch.float32)
+    q = si.normal((B, Hq, d), d, "q", device=DEV)
+    table = torch.arange(B * pages, dtype=torch.int32, device=DEV).reshape(B, pages)
+    lens = torch.tensor([L, 77], dtype=torch.int32, device=DEV)
+
+    def off(x):
+        base = torch.zeros(x.numel() + 1, dtype=x.dtype, device=DEV)
+        base[1:] = x.reshape(-1)
+        return base[1:].view(x.shape)
+
+    def flat(x):
+        return x.reshape((B, pages) + x.shape[1:]).transpose(1, 2).reshape(B, Hkv, pages * P, x.shape[-1]).contiguous()
+    kw = dict(seq_len=lens, o_dtype=torch.float32)
+    want = sfa.sfa_attn_decode_paged(ci, cv, vc, table, q=q, **kw)
+    qc = sfa.sfa_topk_encode(q, k)
+    got = [sfa.sfa_attn_decode_paged(*(off(x) for x in (ci, cv, vc)), table, q=q, **kw),
+           sfa.sfa_attn_decode(*qc, *(off(flat(x)) for x in (ci, cv, vc)), **kw)]
+    torch.cuda.synchronize()
+    for o, lse in got:
+        assert (o - want[0]).abs().max() <= TOL_O_F32 and (lse - want[1]).abs().max() <= 1e-5
+
+
 def test_float32_cache_values():
     _case(2, 4, 1, 700, 128, 16, True, [700, 333], seed=3, cache_bf16=False)
 
