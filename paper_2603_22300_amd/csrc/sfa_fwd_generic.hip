@@ -22,19 +22,23 @@
 // two wavefronts of a row group split the keys and merge by their LSE at the
 // end: that halves the serial chain of the longest causal block, which sets
 // the time of sequences of a few thousand tokens, and gives each SIMD two
-// waves.  d > 128 (KG = 1, 4 wavefronts) needs the registers of one wave per
-// SIMD for its operands.  Rows, V and O of any alignment (vec: 16-byte loads
-// where d and the arrays allow).
+// waves.  d > 128 (KG = 1, 4 wavefronts) has one wave per SIMD for its operands
+// and still spills with 32-bit codes: 73 registers (292 bytes of scratch a lane) with
+// bf16 V, 96 (388) with float32 V; 16-bit codes spill none, and at d in (96, 128]
+// float32 V spills 16.  Rows, V and O of any alignment (vec: 16-byte loads where d and
+// the arrays allow).
 //
 // Bound by the chain of one tile (stage, scores, softmax, P.V, barrier: about
-// 5 us with 48 + 16 MFMAs per wavefront and 32 x 32 tile at d = 128, 3.5 with
-// 16-bit codes' 8 + 16) at two waves per SIMD.  Measured against the float32
+// 5.3 us with 48 + 24 MFMAs per wavefront and 32 x 32 tile at d = 128, 4 with
+// 16-bit codes' 8 + 24) at two waves per SIMD.  Measured against the float32
 // vector-unit kernel it replaces (k + 2d multiply-adds per pair, 32 rows per
-// workgroup), us per call: 2 x 12 heads over 4 KV heads, n = 1535, d = 128, k =
-// 16: 2549 -> 150 (16-bit codes 2540 -> 97); 4 x 8 heads, n = 1000, d = 96: 981
-// -> 67; 8 heads, n = 1000: d = 256 1545 -> 225, d = 192 with float32 V 1272 ->
-// 300; 5 heads, n = 100: 121 -> 19.  Letting one wavefront of a SIMD stage
-// while the other computes did not change these (150 -> 146, 97 -> 101).
+// workgroup), us per call: batch 2, 12 query over 2 KV heads, n = 1535, d = 128, k =
+// 16: 2528 -> 150 (16-bit codes 2536 -> 110, float32 V and O 2573 -> 204); batch 4, 8
+// heads, n = 1000, d = 96: 974 -> 68; 8 heads, n = 1000: d = 256 1546 -> 230, d = 192
+// with float32 V 1269 -> 297; 5 heads, n = 100: 82 -> 14.5.  Of these the third piece of
+// P, the sums that keep the error at the other kernel's and the exact maximum take 5%
+// (16-bit codes 15%).  Letting one wavefront of a SIMD stage while the other
+// computes changed nothing.
 #include <math.h>
 
 #include <algorithm>
