@@ -11,8 +11,8 @@
 // step (32 query over 8 KV heads, d = 128, k = 16), all in 4096-key chunks ->
 // now: one sequence of 3000 keys 40.1 -> 11.0 us (8 -> 96 workgroups), 64,000
 // keys 46.3 -> 33.3; 64 x 16K keys under a 4096-key window 175 -> 153, a
-// 1000-key window 103 -> 51; 8-bit cache with its append, 64 x 4096 keys 125
-// -> 74.  Aiming at 512 or 1024 workgroups without a window was slower (64,000
+// 1000-key window 103 -> 51; 8-bit cache with its append, 64 mixed lengths to 4096
+// 125 -> 74.  Aiming at 512 or 1024 workgroups without a window was slower (64,000
 // keys 35.0 and 36.7 us, 16 x 2000 keys 21.9 and 23.6 against 20.5): each
 // workgroup pays its prologue and its partial.
 //   scores: lane = key.  The G query codes are densified once into an LDS
